@@ -37,7 +37,7 @@ def listed():
         {"name": "select_6m", "kind": "select", "rows": 6_000_007, "preds": 8},
         # the same on the full fact table: the framework's main path
         {"name": "select_60m", "kind": "select", "rows": 60_000_000, "preds": 8},
-        # a weakly selective selection kept whole, without a count before it: the write pass
+        # two weakly selective selections kept whole in turn, without counts before them
         {"name": "materialize_20m", "kind": "materialize", "rows": 20_000_003, "sel": 0.35, "proj": 3},
         # split selectivities of conjunctions for predicate ordering
         {"name": "conjuncts_10m", "kind": "conjuncts", "rows": 10_000_019, "preds": 4},
@@ -222,19 +222,20 @@ def _prepare_select(case, seed):
 def _materialize_inputs(case, seed):
     n = case["rows"]
     t = dg.table_plain(n, seed=seed * 7 + 1, device=DEV)
-    # a range of the permutation key: exactly k rows, evenly spread
+    # two ranges of the permutation key: exactly k rows each, evenly spread
     k = max(1, int(case["sel"] * n))
-    a = int(np.random.default_rng(seed * 7 + 2).integers(0, n - k + 1))
-    return t, ("between", 0, a, a + k - 1), k, [1, 2, 3, 0][:case["proj"]]
+    rng = np.random.default_rng(seed * 7 + 2)
+    specs = [("between", 0, int(a), int(a) + k - 1) for a in rng.integers(0, n - k + 1, 2)]
+    return t, specs, k, [1, 2, 3, 0][:case["proj"]]
 
 
 def _prepare_materialize(case, seed):
-    t, spec, k, proj = _materialize_inputs(case, seed)
+    t, specs, k, proj = _materialize_inputs(case, seed)
     ctx, dt = esc.Context(0), _device_table(t)
-    return {"ctx": ctx, "table": dt, "pred": esc.Pred(dt, spec), "proj": proj,
-            # room as an estimate would give it: a tenth more than qualifies
-            "ids": torch.zeros(k + k // 10 + 1, dtype=torch.int32, device=DEV),
-            "outs": [torch.zeros(k + k // 10 + 1, dtype=torch.int32, device=DEV) for _ in proj],
+    room = k + k // 10 + 1   # as an estimate would give it: a tenth more than qualifies
+    return {"ctx": ctx, "table": dt, "preds": [esc.Pred(dt, p) for p in specs], "proj": proj,
+            "ids": [torch.zeros(room, dtype=torch.int32, device=DEV) for _ in specs],
+            "outs": [[torch.zeros(room, dtype=torch.int32, device=DEV) for _ in proj] for _ in specs],
             "ws": ctx.workspace(dt, esc.WS_MATERIALIZE), "stream": torch.cuda.current_stream()}
 
 
@@ -367,9 +368,11 @@ def _run_select(s):
 
 
 def _run_materialize(s):
-    c = s["ctx"].materialize(s["table"], s["pred"], s["proj"], s["ids"], s["outs"], s["ids"].numel(), ws=s["ws"],
-                             stream=s["stream"])
-    return [c, s["ids"][:c]] + [o[:c] for o in s["outs"]]
+    out = []
+    for p, ids, cols in zip(s["preds"], s["ids"], s["outs"]):
+        c = s["ctx"].materialize(s["table"], p, s["proj"], ids, cols, ids.numel(), ws=s["ws"], stream=s["stream"])
+        out.append([c, ids[:c]] + [v[:c] for v in cols])
+    return out
 
 
 def _run_conjuncts(s):
@@ -420,7 +423,7 @@ def work(case):
     if kind == "count":
         return {"bytes": case["preds"] * 3 * 4 * n, "flops": 0}
     if kind == "materialize":
-        return {"bytes": 4 * n + case["sel"] * n * 4 * (2 * case["proj"] + 1), "flops": 0}
+        return {"bytes": 2 * (4 * n + case["sel"] * n * 4 * (2 * case["proj"] + 1)), "flops": 0}
     if kind == "planning":
         rows = (max(1000, n // 100) + max(1000, n // 10) + (n if case["probe"] else 0))
         return {"bytes": -(-case["queries"] // 64) * rows * 16, "flops": 0}
@@ -506,8 +509,8 @@ def _exact_select(case, seed):
 
 
 def _exact_materialize(case, seed):
-    t, spec, _, proj = _materialize_inputs(case, seed)
-    return _kept(t.cols, spec, proj)
+    t, specs, _, proj = _materialize_inputs(case, seed)
+    return [_kept(t.cols, p, proj) for p in specs]
 
 
 def _exact_conjuncts(case, seed):
