@@ -315,9 +315,12 @@ int esc_count_conjuncts(esc_ctx *ctx, const esc_table *t, const esc_pred *p, voi
 /* ------------------------------------------------------------------ batched
  *
  * Section 2 runs one selectivity sub-query for every table that carries a
- * selection; this runs many such sub-queries at once.  One persistent kernel
- * reads each table's columns once per predicate group and counts every
- * predicate of the group; the whole launch is captured in a hipGraph.
+ * selection; this runs many such sub-queries at once.  Persistent kernels
+ * read each table's columns once per predicate group and count every
+ * predicate of the group: a group of up to 128 predicates through a predicate
+ * index where that is estimated to be cheaper (udf predicates never are),
+ * the others by interpreting their programs; the whole launch is captured in
+ * a hipGraph.
  * The batch keeps the tables' column pointers; its device memory (work
  * list, programs, counters) is a caller-owned workspace of at least
  * esc_batch_workspace_size() bytes, 256-byte aligned, that must outlive the
@@ -326,7 +329,8 @@ typedef struct {
     int32_t autotune;        /* 1: time candidate configurations at create */
     int32_t block;           /* threads per block (256 or 512); 0 = default */
     int32_t rows_per_thread; /* 8 or 16; other values = 8 */
-    int32_t group;           /* predicates evaluated per pass over a chunk; 0 = all of the table's */
+    int32_t group;           /* predicates evaluated per pass over a chunk; 0 = all of the table's
+                                (at most 128 where an index counts them) */
     int32_t chunk_rows;      /* rows per work item; 0 = about 8 items per block of the grid */
     int32_t blocks_per_cu;   /* persistent blocks per compute unit; 0 = default */
     int32_t max_preds;       /* predicates the batch may hold after esc_batch_update; 0 = npreds */

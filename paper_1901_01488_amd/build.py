@@ -22,12 +22,14 @@ ARCH = "gfx950"
 SOURCES = [
     "esc_compile.cpp",
     "esc_features.cpp",
+    "esc_index.cpp",
     "esc_policy.cpp",
     "esc_types.cpp",
     "esc_api.hip",
     "esc_count.hip",
     "esc_materialize.hip",
     "esc_batch.hip",
+    "esc_index.hip",
     "esc_join.hip",
     "esc_mlp.hip",
 ]

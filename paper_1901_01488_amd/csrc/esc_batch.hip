@@ -12,7 +12,11 @@
 // in LDS and reach the global u64 counters with one atomic per predicate per
 // item.  Counts are exact and independent of the order of the additions.
 //
-// The launch (zero counters -> persistent kernel -> copy of the counts to
+// Groups of many predicates are counted by a predicate index instead
+// (esc_index.hip), where the planner's cost estimate says that it is cheaper;
+// the two kernels have a work list each.
+//
+// The launch (zero counters -> persistent kernels -> copy of the counts to
 // pinned host memory) is captured once into a hipGraph; a count is one
 // graph launch and one stream synchronisation.  Block shape, rows per thread,
 // group size and chunk length are chosen by timing candidate plans on the
@@ -30,8 +34,10 @@
 #include <string>
 #include <vector>
 
+#include "esc_batch.h"
 #include "esc_device.h"
 #include "esc_host.h"
+#include "esc_index.h"
 #include "esc_kernels.h"
 #include "esc_runtime.h"
 
@@ -44,12 +50,6 @@ struct BatchGroup {
     int32_t K;
     int32_t npred;
     int32_t pbegin;   // first program / predicate id of the group
-    int32_t pad;
-};
-
-struct BatchItem {
-    int32_t group;
-    int32_t r0, r1;
     int32_t pad;
 };
 
@@ -129,19 +129,21 @@ __device__ __forceinline__ void run_group(const BatchGroup &g, const BatchItem &
 // a group's K <= KM columns are dispatched to a body compiled for K, so the
 // kernel's registers (and the waves a SIMD holds) follow from KM.
 template <int RPT, bool UDF, int KM>
-__global__ __launch_bounds__(kScanBlock) void batch_kernel(const BatchGroup *__restrict__ groups,
-                                                           const BatchItem *__restrict__ items,
-                                                           const Program *__restrict__ progs,
-                                                           const int32_t *__restrict__ pred_ids,
-                                                           unsigned long long *counts, unsigned int *queue)
+__global__ __launch_bounds__(kScanBlock) void batch_kernel(BatchHeader *h, const char *__restrict__ lists,
+                                                           unsigned long long *counts)
 {
     constexpr int NW = kScanBlock / 64;
     __shared__ uint32_t s_cnt[kMaxGroup][NW];
     __shared__ int s_item;
-    const int nitems = (int)queue[1];   // written by the host with the plan
+    // the header and the lists were written by the host with the plan
+    const int nitems = (int)h->nitems[0];
+    const BatchGroup *__restrict__ groups = (const BatchGroup *)(lists + h->groups);
+    const BatchItem *__restrict__ items = (const BatchItem *)(lists + h->items);
+    const Program *__restrict__ progs = (const Program *)(lists + h->progs);
+    const int32_t *__restrict__ pred_ids = (const int32_t *)(lists + h->ids);
     for (int i = threadIdx.x; i < kMaxGroup * NW; i += kScanBlock) (&s_cnt[0][0])[i] = 0;
     for (;;) {
-        if (threadIdx.x == 0) s_item = (int)atomicAdd(queue, 1u);
+        if (threadIdx.x == 0) s_item = (int)atomicAdd(&h->next[0], 1u);
         __syncthreads();
         const int item = __builtin_amdgcn_readfirstlane(s_item);
         if (item >= nitems) break;
@@ -180,8 +182,7 @@ __global__ __launch_bounds__(kScanBlock) void batch_kernel(const BatchGroup *__r
     }
 }
 
-typedef void (*BatchFn)(const BatchGroup *, const BatchItem *, const Program *, const int32_t *,
-                        unsigned long long *, unsigned int *);
+typedef void (*BatchFn)(BatchHeader *, const char *, unsigned long long *);
 
 template <int KM>
 static BatchFn batch_fn_km(int rpt, bool udf)
@@ -195,10 +196,10 @@ static BatchFn batch_fn(int rpt, bool udf, int km)
     return km <= 4 ? batch_fn_km<4>(rpt, udf) : km <= 6 ? batch_fn_km<6>(rpt, udf) : batch_fn_km<8>(rpt, udf);
 }
 
-__global__ void batch_zero_kernel(unsigned long long *counts, int n, unsigned int *queue)
+__global__ void batch_zero_kernel(unsigned long long *counts, int n, BatchHeader *h)
 {
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) counts[i] = 0ull;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *queue = 0u;
+    if (blockIdx.x == 0 && threadIdx.x < 2) h->next[threadIdx.x] = 0u;
 }
 
 }  // namespace esc
@@ -212,10 +213,15 @@ struct TableInfo {
 };
 
 struct Plan {
+    // the interpreter's groups
     std::vector<BatchGroup> groups;
     std::vector<BatchItem> items;
     std::vector<Program> progs;
-    std::vector<int32_t> pred_ids;
+    std::vector<int32_t> pred_ids;   // of the interpreter's programs, then of the indexed groups
+    // groups counted by a predicate index
+    std::vector<IndexGroupRef> igroups;
+    std::vector<BatchItem> iitems;
+    std::vector<uint32_t> blob;
 };
 
 struct esc_batch {
@@ -223,22 +229,18 @@ struct esc_batch {
     int device = 0;                      // kept so that destruction never touches ctx
     std::vector<TableInfo> tables;
     std::vector<int32_t> pred_table;
-    std::vector<Program> src;            // compiled programs as given
+    std::vector<const Program *> src;    // the callers' compiled programs, during a call that plans them
     std::vector<int> constant;           // 0: scanned; 1: always true; -1: always false or empty table
     esc_batch_opts opts{};
     int nkernel = 0;                     // predicates evaluated by the kernel
-    // device state: fixed regions of the caller's workspace
-    BatchGroup *d_groups = nullptr;
-    BatchItem *d_items = nullptr;
-    Program *d_progs = nullptr;
-    int32_t *d_pred_ids = nullptr;
+    // device state: regions of the caller's workspace
     unsigned long long *d_counts = nullptr;
-    unsigned int *d_queue = nullptr;     // [0] next item, [1] number of items
+    BatchHeader *d_head = nullptr;       // the plan: header, then its lists
     size_t cap_counts = 0;               // predicates the regions hold (the counters the graph zeroes and copies)
-    size_t cap_items = 0;                // work items the item region holds
+    size_t cap_plan = 0;                 // bytes the plan may take
     const void *graph_fn = nullptr;      // kernel the captured graph launches
     unsigned long long *h_counts = nullptr;   // pinned host memory, cap_counts entries
-    int nitems = 0;
+    bool has_interp = false, has_index = false;   // kernels of the captured graph
     int grid = 0;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -272,59 +274,195 @@ int slot_limit(const esc_batch *b, const esc_batch_opts &o)
 {
     int need = std::max(1, (int)o.max_cols);
     for (size_t p = 0; p < b->src.size(); p++)
-        if (b->constant[p] == 0) need = std::max(need, (int)b->src[p].nslots);
+        if (b->constant[p] == 0) need = std::max(need, (int)b->src[p]->nslots);
     return need <= 4 ? 4 : need <= 6 ? 6 : 8;
 }
 
 // chunk_rows == 0 sizes the chunks so that the plan has about eight items
 // per block of the persistent grid (load balance at the end of the launch),
 // but no fewer than 8 block tiles per item (the per-item cost of the atomic
-// pop and of publishing the group's counts stays small).
-int64_t chunk_rows_for(const esc_batch *b, const esc_batch_opts &o, int gmax, int grid)
+// pop and of publishing the group's counts stays small).  npreds: predicates
+// of each table that the interpreter counts.
+int64_t chunk_rows_for(const esc_batch *b, const esc_batch_opts &o, int gmax, int grid,
+                       const std::vector<int64_t> &npreds)
 {
     const int tile = tile_rows(o.rows_per_thread);
     int64_t chunk = o.chunk_rows;
     if (chunk <= 0) {
         int64_t rows = 0;
-        for (size_t t = 0; t < b->tables.size(); t++) {
-            int64_t np = 0;
-            for (size_t p = 0; p < b->pred_table.size(); p++) np += b->pred_table[p] == (int)t && b->constant[p] == 0;
-            rows += b->tables[t].nrows * ((np + gmax - 1) / gmax);   // a lower bound on the groups of the table
-        }
+        for (size_t t = 0; t < b->tables.size(); t++)
+            rows += b->tables[t].nrows * ((npreds[t] + gmax - 1) / gmax);   // a lower bound on the groups of the table
         chunk = std::max<int64_t>(rows / (8 * (int64_t)std::max(grid, 1)), 8 * (int64_t)tile);
         chunk = std::min<int64_t>(chunk, 1 << 21);
     }
     return (chunk + tile - 1) / tile * tile;
 }
 
-int build_plan(const esc_batch *b, const esc_batch_opts &o, int grid, Plan &plan)
+// Device time of one predicate in the interpreter and of an indexed group, in
+// cycles of one CU per 64 rows.  Measured: 17.5 and 25 per predicate of 3.3 and
+// 2.9 instructions (16 rows per lane, four columns; 8 rows, six); 243 for 64
+// predicates on four columns and 375 for 128 on six (7.5 levels on average).
+double interp_cost(const Program &P) { return 5.0 + 5.0 * P.ninsn; }
+
+double index_cost(const IndexGroup &g)
+{
+    double c = 6.0 * g.words;
+    for (int k = 0; k < g.ncols; k++) c += 12.0 + 4.5 * g.cols[k].levels + 4.0 * g.rec;
+    return c;
+}
+
+// How much cheaper than the interpreter an index must be when predicates are
+// left to the interpreter: the two kernels run one after the other.  Where
+// every predicate of the batch goes to an index, and the interpreter's items of
+// 16K rows would not fill the chip, each of them still taking its predicates
+// one after the other, an index of a few predicates pays from half the
+// estimated gain (three tables of up to 1M rows: 4 predicates on each 152
+// against 213 us, 8 161 against 256; 2 on each 175 against 170).
+constexpr double kIndexGain = 1.25, kIndexGainSmall = 0.5;
+constexpr int kIndexFewest = 4;
+
+bool fills_chip(const esc_batch *b, int64_t nrows) { return nrows >= 16384ll * b->ctx->num_cus; }
+
+int index_grid(const esc_batch *b) { return std::max(1, b->ctx->num_cus * kIndexBlocksPerCu); }
+
+// Takes the predicates of each table's members that a predicate index counts
+// more cheaply than the interpreter out of members and into the plan.  Groups
+// are formed in the order of the predicates' OR clauses, so that predicates
+// with as many of them share the extra record words.
+// small: whether the rule for small tables may be used; true if it was.
+bool plan_index(const esc_batch *b, const esc_batch_opts &o, bool small, std::vector<std::vector<int>> &members,
+                Plan &plan)
+{
+    bool used_small = false;
+    const int gmax = o.group > 0 ? std::min((int)o.group, kIndexMaxPreds) : kIndexMaxPreds;
+    struct Planned { size_t table; double cost; };
+    std::vector<Planned> planned;
+    double total = 0.0;
+    for (size_t t = 0; t < members.size(); t++) {
+        const TableInfo &T = b->tables[t];
+        std::vector<int> &mem = members[t];
+        IndexSource src;
+        plan.blob.reserve(plan.blob.size() + mem.size() * 96);   // about what 128 predicates take
+        for (int p : mem) src.add(*b->src[p], T.dtypes.data());
+        std::vector<int> order, at;   // positions in mem
+        for (int i = 0; i < (int)mem.size(); i++)
+            if (src.preds[i].nor >= 0) order.push_back(i);
+        std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return src.preds[x].nor < src.preds[y].nor; });
+        std::vector<char> taken(mem.size(), 0);
+        for (size_t i = 0; i < order.size();) {
+            int n = (int)std::min<size_t>(gmax, order.size() - i);
+            IndexGroup g;
+            const size_t blob0 = plan.blob.size();
+            // fewer predicates need fewer boundaries, columns and layers
+            while (n > 0 && !build_index(src, &order[i], n, T.dtypes.data(), g, plan.blob)) n = n > 32 ? n / 64 * 32 : n / 2;
+            if (n == 0) {
+                i++;
+                continue;
+            }
+            double by_interp = 0.0;
+            for (int j = 0; j < n; j++) by_interp += interp_cost(*b->src[mem[order[i + j]]]);
+            const double cost = index_cost(g);
+            if (kIndexGain * cost > by_interp) {
+                if (!small || n < kIndexFewest || fills_chip(b, T.nrows) || kIndexGainSmall * cost > by_interp) {
+                    plan.blob.resize(blob0);
+                    i += n;
+                    continue;
+                }
+                used_small = true;
+            }
+            IndexGroupRef r{};
+            r.words = g.words;
+            r.rec = g.rec;
+            r.nor = g.nor;
+            r.ncols = g.ncols;
+            r.nwords = g.nwords;
+            r.blob = (uint32_t)blob0;
+            r.npred = n;
+            r.pbegin = (int)plan.pred_ids.size();
+            memcpy(r.or_word, g.or_word, sizeof r.or_word);
+            for (int k = 0; k < g.ncols; k++)
+                r.cols[k] = IndexColumnRef{(const uint32_t *)T.cols[g.cols[k].col], 4u * (uint32_t)g.cols[k].key_off,
+                                           4u * (uint32_t)g.cols[k].rec_off, g.cols[k].levels, g.cols[k].is_float};
+            plan.igroups.push_back(r);
+            planned.push_back({t, cost});
+            total += cost * (double)T.nrows;
+            for (int j = 0; j < n; j++) {
+                plan.pred_ids.push_back(mem[order[i + j]]);
+                taken[order[i + j]] = 1;
+            }
+            i += n;
+        }
+        for (int i = 0; i < (int)mem.size(); i++)
+            if (!taken[i]) at.push_back(mem[i]);
+        mem.swap(at);
+    }
+    // About six items of equal cost per block of the persistent grid, each of
+    // at least four wave tiles per wave (an item ends with a sum over lanes);
+    // with less work than that, one item per block.
+    constexpr int64_t kStep = kIndexTile * (kIndexBlock / 64);
+    struct Cost { double cost; BatchItem it; };
+    std::vector<Cost> items;
+    for (size_t gi = 0; gi < planned.size(); gi++) {
+        const int64_t nrows = b->tables[planned[gi].table].nrows;
+        const double per_block = total / index_grid(b) / planned[gi].cost;   // rows
+        int64_t chunk = (int64_t)std::max(per_block / 6.0, std::min(per_block, 4.0 * kStep));
+        chunk = std::max<int64_t>(chunk, o.chunk_rows);
+        chunk = std::max<int64_t>(kStep, std::min<int64_t>((chunk + kStep - 1) / kStep * kStep, 1ll << 30));
+        for (int64_t r0 = 0; r0 < nrows; r0 += chunk) {
+            const int64_t r1 = std::min(nrows, r0 + chunk);
+            items.push_back({(double)(r1 - r0) * planned[gi].cost, BatchItem{(int32_t)gi, (int32_t)r0, (int32_t)r1, 0}});
+        }
+    }
+    std::stable_sort(items.begin(), items.end(), [](const Cost &a, const Cost &c) { return a.cost > c.cost; });
+    for (auto &c : items) plan.iitems.push_back(c.it);
+    return used_small;
+}
+
+// use_index: whether predicate indexes may take predicates from the
+// interpreter; lists: false leaves the programs out (to size a workspace)
+int build_plan(const esc_batch *b, const esc_batch_opts &o, int grid, bool use_index, bool lists, Plan &plan)
 {
     plan = Plan{};
     const int gmax = o.group > 0 ? std::min(o.group, kMaxGroup) : kMaxGroup;
     const int kmax = slot_limit(b, o);
-    const int64_t chunk = chunk_rows_for(b, o, gmax, grid);
+    std::vector<std::vector<int>> members(b->tables.size());
+    for (size_t p = 0; p < b->pred_table.size(); p++)
+        if (b->constant[p] == 0) members[b->pred_table[p]].push_back((int)p);
+    if (use_index) {
+        const std::vector<std::vector<int>> all = members;
+        if (plan_index(b, o, true, members, plan) &&
+            std::any_of(members.begin(), members.end(), [](const std::vector<int> &m) { return !m.empty(); })) {
+            plan = Plan{};
+            members = all;
+            plan_index(b, o, false, members, plan);
+        }
+    }
+    // the interpreter's predicate ids come first in its own numbering
+    const std::vector<int32_t> index_ids = std::move(plan.pred_ids);
+    plan.pred_ids.clear();
+    std::vector<int64_t> npreds;
+    for (auto &m : members) npreds.push_back((int64_t)m.size());
+    const int64_t chunk = chunk_rows_for(b, o, gmax, grid, npreds);
     struct Cost { int64_t cost; BatchItem it; };
     std::vector<Cost> items;
     for (size_t t = 0; t < b->tables.size(); t++) {
         const TableInfo &T = b->tables[t];
-        std::vector<int> members;
-        for (size_t p = 0; p < b->pred_table.size(); p++)
-            if (b->pred_table[p] == (int)t && b->constant[p] == 0) members.push_back((int)p);
+        const std::vector<int> &mine = members[t];
         size_t i = 0;
-        while (i < members.size()) {
+        while (i < mine.size()) {
             int gslot[64];
             for (int c = 0; c < 64; c++) gslot[c] = -1;
             int gcols[kMaxSlots];
             int K = 0;
             std::vector<int> mem;
-            while (i < members.size() && (int)mem.size() < gmax) {
-                const Program &P = b->src[members[i]];
+            while (i < mine.size() && (int)mem.size() < gmax) {
+                const Program &P = *b->src[mine[i]];
                 int add = 0;
                 for (int s = 0; s < P.nslots; s++) add += gslot[P.slot_col[s]] < 0;
                 if (K + add > kmax) break;
                 for (int s = 0; s < P.nslots; s++)
                     if (gslot[P.slot_col[s]] < 0) { gslot[P.slot_col[s]] = K; gcols[K++] = P.slot_col[s]; }
-                mem.push_back(members[i]);
+                mem.push_back(mine[i]);
                 i++;
             }
             BatchGroup g{};
@@ -334,7 +472,8 @@ int build_plan(const esc_batch *b, const esc_batch_opts &o, int grid, Plan &plan
             g.npred = (int)mem.size();
             g.pbegin = (int)plan.progs.size();
             for (int p : mem) {
-                plan.progs.push_back(remap(b->src[p], gslot, g.K, gcols));
+                if (!lists) break;
+                plan.progs.push_back(remap(*b->src[p], gslot, g.K, gcols));
                 plan.pred_ids.push_back(p);
             }
             const int gid = (int)plan.groups.size();
@@ -348,25 +487,64 @@ int build_plan(const esc_batch *b, const esc_batch_opts &o, int grid, Plan &plan
     }
     std::stable_sort(items.begin(), items.end(), [](const Cost &a, const Cost &c) { return a.cost > c.cost; });
     for (auto &c : items) plan.items.push_back(c.it);
+    for (IndexGroupRef &r : plan.igroups) r.pbegin += (int32_t)plan.pred_ids.size();
+    plan.pred_ids.insert(plan.pred_ids.end(), index_ids.begin(), index_ids.end());
     return ESC_OK;
 }
 
-// Regions of a batch workspace for pcap predicates and icap work items.
+size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+template <typename T>
+size_t list_bytes(const std::vector<T> &v) { return up256(v.size() * sizeof(T)); }
+
+// Bytes of a plan in the workspace: header and lists.
+size_t plan_bytes(const Plan &p)
+{
+    return sizeof(BatchHeader) + list_bytes(p.pred_ids) + list_bytes(p.groups) + list_bytes(p.items) +
+           list_bytes(p.progs) + list_bytes(p.igroups) + list_bytes(p.iitems) + list_bytes(p.blob);
+}
+
+// The plan as the kernels read it.
+void pack_plan(const Plan &p, std::vector<char> &out)
+{
+    out.assign(plan_bytes(p), 0);
+    BatchHeader h{};
+    h.nitems[0] = (unsigned int)p.items.size();
+    h.nitems[1] = (unsigned int)p.iitems.size();
+    size_t at = sizeof(BatchHeader);
+    auto put = [&](const auto &v, unsigned int &off) {
+        off = (unsigned int)at;
+        if (!v.empty()) memcpy(out.data() + at, v.data(), v.size() * sizeof v[0]);
+        at += list_bytes(v);
+    };
+    put(p.pred_ids, h.ids);
+    put(p.groups, h.groups);
+    put(p.items, h.items);
+    put(p.progs, h.progs);
+    put(p.igroups, h.igroups);
+    put(p.iitems, h.iitems);
+    put(p.blob, h.blob);
+    memcpy(out.data(), &h, sizeof h);
+}
+
+// Regions of a batch workspace for pcap predicates: counters, then the plan.
 struct BatchLayout {
-    size_t queue, counts, ids, progs, groups, items, bytes;
+    size_t counts, plan, bytes;
 };
 
-BatchLayout batch_layout(size_t pcap, size_t icap)
+// items: work items of the interpreter when it counts every predicate.  An
+// index takes the place of its predicates' programs (at most 77 KB for what
+// would be 128 programs of 2 KB, and groups of fewer are chosen only over
+// programs that take longer); its work items are extra.
+BatchLayout batch_layout(const esc_batch *b, size_t pcap, size_t items)
 {
-    auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
     BatchLayout L;
-    L.queue = 0;
-    L.counts = 256;
-    L.ids = up(L.counts + pcap * sizeof(unsigned long long));
-    L.progs = up(L.ids + pcap * sizeof(int32_t));
-    L.groups = up(L.progs + pcap * sizeof(Program));
-    L.items = up(L.groups + pcap * sizeof(BatchGroup));
-    L.bytes = up(L.items + icap * sizeof(BatchItem));
+    L.counts = 0;
+    L.plan = up256(pcap * sizeof(unsigned long long));
+    L.bytes = L.plan + sizeof(BatchHeader) + up256(pcap * sizeof(int32_t)) + up256(pcap * sizeof(BatchGroup)) +
+              up256(pcap * sizeof(Program)) + up256(items * sizeof(BatchItem)) +
+              up256((7 * (size_t)index_grid(b) + pcap) * sizeof(BatchItem)) +
+              up256((b->tables.size() + pcap / 32 + 1) * sizeof(IndexGroupRef)) + 8 * 256;
     return L;
 }
 
@@ -392,16 +570,12 @@ void destroy_graph(esc_batch *b)
     b->graph = nullptr;
 }
 
-// Uploads a plan; captures zero -> kernel -> copy into a graph unless the
-// graph of an earlier plan still fits (same buffers, kernel shape and counter
-// capacity): the item count lives in device memory, so a new plan of the
-// same shape costs a few small copies and no capture.
-// The kernel a batch launches: rows per thread, and udf support when any
+// The interpreter kernel a batch launches: rows per thread, and udf support when any
 // scanned predicate has a udf.
 BatchFn batch_kernel_for(const esc_batch *b, const esc_batch_opts &o)
 {
     bool udf = false;
-    for (size_t p = 0; p < b->src.size(); p++) udf |= b->constant[p] == 0 && (b->src[p].flags & P_HAS_UDF) != 0;
+    for (size_t p = 0; p < b->src.size(); p++) udf |= b->constant[p] == 0 && (b->src[p]->flags & P_HAS_UDF) != 0;
     return batch_fn(o.rows_per_thread, udf, slot_limit(b, o));
 }
 
@@ -455,45 +629,49 @@ std::vector<esc_batch_opts> candidates(const esc_batch *b, const esc_batch_opts 
     return out;
 }
 
+// Uploads a plan (one copy); captures zero -> kernels -> copy into a graph
+// unless the graph of an earlier plan still fits (same buffers, kernels and
+// counter capacity): the item counts live in device memory, so a new plan of
+// the same shape needs no capture.
 int install(esc_batch *b, const esc_batch_opts &o)
 {
     BatchFn fn = batch_kernel_for(b, o);
     const int grid = plan_grid(b, o);
     Plan plan;
-    int rc = build_plan(b, o, grid, plan);
+    int rc = build_plan(b, o, grid, true, true, plan);
     if (rc) return rc;
-    if (plan.items.size() > b->cap_items)
-        return fail(ESC_ERR_OOM, "the plan has %zu work items, the workspace holds %zu", plan.items.size(),
-                    b->cap_items);
+    // predicate indexes that do not fit the workspace give way to programs
+    if (plan_bytes(plan) > b->cap_plan && !plan.igroups.empty() && (rc = build_plan(b, o, grid, false, true, plan))) return rc;
+    if (plan_bytes(plan) > b->cap_plan)
+        return fail(ESC_ERR_OOM, "the plan takes %zu bytes (%zu work items), the workspace holds %zu", plan_bytes(plan),
+                    plan.items.size() + plan.iitems.size(), b->cap_plan);
     hipStream_t s = b->cap_stream;
-    const unsigned int nitems = (unsigned int)plan.items.size();
-    if ((rc = hipchk(hipMemcpyAsync(b->d_groups, plan.groups.data(), plan.groups.size() * sizeof(BatchGroup),
-                                    hipMemcpyHostToDevice, s), "upload groups"))) return rc;
-    if ((rc = hipchk(hipMemcpyAsync(b->d_items, plan.items.data(), plan.items.size() * sizeof(BatchItem),
-                                    hipMemcpyHostToDevice, s), "upload items"))) return rc;
-    if ((rc = hipchk(hipMemcpyAsync(b->d_progs, plan.progs.data(), plan.progs.size() * sizeof(Program),
-                                    hipMemcpyHostToDevice, s), "upload programs"))) return rc;
-    if ((rc = hipchk(hipMemcpyAsync(b->d_pred_ids, plan.pred_ids.data(), plan.pred_ids.size() * sizeof(int32_t),
-                                    hipMemcpyHostToDevice, s), "upload ids"))) return rc;
-    if ((rc = hipchk(hipMemcpyAsync(b->d_queue + 1, &nitems, sizeof nitems, hipMemcpyHostToDevice, s),
-                     "upload item count"))) return rc;
+    std::vector<char> packed;
+    pack_plan(plan, packed);
+    if ((rc = hipchk(hipMemcpyAsync(b->d_head, packed.data(), packed.size(), hipMemcpyHostToDevice, s), "upload plan")))
+        return rc;
     if ((rc = hipchk(hipStreamSynchronize(s), "upload sync"))) return rc;
-    b->nitems = (int)nitems;
     b->opts = o;
     b->opts.blocks_per_cu = grid / std::max(1, b->ctx->num_cus);
     b->opts.max_cols = slot_limit(b, o);
     // the graph bakes in the workspace regions (fixed for the batch's
-    // lifetime), the counter capacity and the kernel
-    const bool reuse = b->exec && grid == b->grid && b->graph_fn == (const void *)fn;
+    // lifetime), the counter capacity and the kernels
+    const bool interp = !plan.items.empty(), index = !plan.iitems.empty();
+    const bool reuse = b->exec && grid == b->grid && b->graph_fn == (const void *)fn && b->has_interp == interp &&
+                       b->has_index == index;
     if (reuse) return ESC_OK;
     destroy_graph(b);
     b->grid = grid;
+    b->has_interp = interp;
+    b->has_index = index;
+    if (index && (rc = hipchk(prepare_index(), "index kernel LDS"))) return rc;
     const int cap = (int)b->cap_counts;
     if ((rc = hipchk(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal), "begin capture"))) return rc;
     hipLaunchKernelGGL(batch_zero_kernel, dim3(std::max(1, std::min(64, (cap + 255) / 256))), dim3(256), 0, s,
-                       b->d_counts, cap, b->d_queue);
-    hipLaunchKernelGGL(fn, dim3(grid), dim3(kScanBlock), 0, s, b->d_groups, b->d_items, b->d_progs, b->d_pred_ids,
-                       b->d_counts, b->d_queue);
+                       b->d_counts, cap, b->d_head);
+    if (interp)
+        hipLaunchKernelGGL(fn, dim3(grid), dim3(kScanBlock), 0, s, b->d_head, (const char *)b->d_head, b->d_counts);
+    if (index) launch_index(b->d_head, b->d_counts, index_grid(b), s);
     (void)hipMemcpyAsync(b->h_counts, b->d_counts, cap * sizeof(unsigned long long), hipMemcpyDeviceToHost, s);
     hipGraph_t g = nullptr;
     hipError_t e = hipStreamEndCapture(s, &g);
@@ -528,7 +706,7 @@ std::string tune_key(const esc_batch *b)
     for (size_t t = 0; t < b->tables.size(); t++) {
         int np = 0, ni = 0;
         for (size_t p = 0; p < b->pred_table.size(); p++)
-            if (b->pred_table[p] == (int)t) { np++; ni += b->src[p].ninsn; }
+            if (b->pred_table[p] == (int)t) { np++; ni += b->src[p]->ninsn; }
         k += ";" + std::to_string(b->tables[t].nrows) + "x" + std::to_string(b->tables[t].dtypes.size()) + ":" +
              std::to_string(np) + "/" + std::to_string(ni);
     }
@@ -661,7 +839,7 @@ int set_preds(esc_batch *b, const esc_pred *const *preds, int npreds)
         const TableInfo &T = b->tables[b->pred_table[p]];
         if (preds[p]->schema_dtypes != T.dtypes)
             return fail(ESC_ERR_INVALID, "predicate %d was compiled for another schema than table %d", p, b->pred_table[p]);
-        b->src[p] = preds[p]->prog;
+        b->src[p] = &preds[p]->prog;
         const int fl = preds[p]->prog.flags;
         if (T.nrows == 0 || (fl & P_ALWAYS_FALSE)) b->constant[p] = -1;
         else if (fl & P_ALWAYS_TRUE) b->constant[p] = 1;
@@ -702,10 +880,10 @@ int esc_batch_workspace_size(esc_ctx *ctx, const esc_table *const *tables, int n
     size_t items = 0;
     for (const esc_batch_opts &c : candidates(&tmp, o)) {
         Plan plan;
-        if ((rc = build_plan(&tmp, c, plan_grid(&tmp, c), plan))) return rc;
+        if ((rc = build_plan(&tmp, c, plan_grid(&tmp, c), false, false, plan))) return rc;
         items = std::max(items, plan.items.size());
     }
-    *bytes = batch_layout((size_t)std::max(npreds, o.max_preds), items).bytes;
+    *bytes = batch_layout(&tmp, (size_t)std::max(npreds, o.max_preds), items).bytes;
     return ESC_OK;
 }
 
@@ -741,19 +919,14 @@ int esc_batch_create(esc_ctx *ctx, const esc_table *const *tables, int ntables, 
     for (int p = 0; p < npreds; p++)
         if (pred_table[p] < 0 || pred_table[p] >= ntables) { free_batch(b); return fail(ESC_ERR_INVALID, "pred_table[%d] out of range", p); }
     if ((rc = set_preds(b, preds, npreds))) { free_batch(b); return rc; }
-    // fixed regions of the workspace: counters and programs for pcap
-    // predicates, the rest of it for work items
+    // the workspace: counters for pcap predicates, the rest of it for the plan
     const size_t pcap = (size_t)std::max(npreds, o.max_preds);
-    const BatchLayout L0 = batch_layout(pcap, 0);
+    const BatchLayout L0 = batch_layout(b, pcap, 0);
     char *base = (char *)dev_ws;
-    b->d_queue = (unsigned int *)(base + L0.queue);
     b->d_counts = (unsigned long long *)(base + L0.counts);
-    b->d_pred_ids = (int32_t *)(base + L0.ids);
-    b->d_progs = (Program *)(base + L0.progs);
-    b->d_groups = (BatchGroup *)(base + L0.groups);
-    b->d_items = (BatchItem *)(base + L0.items);
+    b->d_head = (BatchHeader *)(base + L0.plan);
     b->cap_counts = pcap;
-    b->cap_items = (ws_bytes - L0.items) / sizeof(BatchItem);
+    b->cap_plan = ws_bytes - L0.plan;
     hipError_t e;
     if ((e = hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking)) != hipSuccess) { free_batch(b); return hip_fail(e, "stream"); }
     if ((e = hipHostMalloc((void **)&b->h_counts, pcap * sizeof(unsigned long long), hipHostMallocDefault)) != hipSuccess) {
@@ -763,6 +936,7 @@ int esc_batch_create(esc_ctx *ctx, const esc_table *const *tables, int ntables, 
     }
     if (o.autotune) rc = autotune(b, (hipStream_t)stream);
     else rc = install(b, o);
+    b->src.clear();
     if (rc) { free_batch(b); return rc; }
     *out = b;
     return ESC_OK;
@@ -785,8 +959,9 @@ int esc_batch_update(esc_batch *b, const esc_pred *const *preds, const int32_t *
         b->pred_table.assign(pred_table, pred_table + npreds);
     }
     int rc = set_preds(b, preds, npreds);
-    if (rc) return rc;
-    return install(b, b->opts);
+    if (!rc) rc = install(b, b->opts);
+    b->src.clear();
+    return rc;
 }
 
 int esc_batch_count(esc_batch *b, void *stream, uint64_t *out_counts)

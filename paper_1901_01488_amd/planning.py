@@ -166,10 +166,9 @@ class Workload:
                 preds = [self.cps[q][t] for q, t in need]
                 owners = [t for _, t in need]
                 if self.batch is None:
-                    # 16 rows per lane, groups of 16 predicates, the
-                    # kernel with four column slots (the tables have four
-                    # columns): the fastest measured for these windows
-                    self.batch = esc.Batch(self.ctx, self.tables, preds, owners, rows_per_thread=16, group=16,
+                    # no limit on the group: a full window's predicates on a
+                    # table share one predicate index
+                    self.batch = esc.Batch(self.ctx, self.tables, preds, owners, rows_per_thread=16,
                                            max_preds=3 * window)
                 else:
                     self.batch.update(preds, owners)
