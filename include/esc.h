@@ -569,10 +569,11 @@ int esc_decimal64_words(const int64_t *values, int64_t n, int32_t *high, int32_t
  * Section 2.2: a left-deep plan probes the largest relation and builds hash
  * tables on the others, whose pushed-down selections (Section 2.1) leave
  * them as temporary tables.  A hash table lives in caller-owned device
- * memory of esc_hash_table_bytes(nkeys) bytes: open addressing with linear
- * probing over a power of two of 8-byte slots, at least two per key and at
- * least 64; several rows may share a key.  The table keeps each key with
- * the index of its build row. */
+ * memory of esc_hash_table_bytes(nkeys) bytes (a power of two of 8-byte
+ * slots, at least two per key and at least 64, and a header); several rows may
+ * share a key.  What the bytes hold is the library's own (a bitmap, row counts
+ * or hashed keys, by the keys' range); they may be copied, but a table is read
+ * only by esc_join_count. */
 int esc_hash_table_bytes(int64_t nkeys, size_t *bytes);
 /* Clears the table and inserts dev_keys[0 .. nkeys) (device int32), enqueued
  * on `stream`.  Errors: ESC_ERR_INVALID (null pointers, nkeys < 0, a size not
@@ -584,9 +585,9 @@ int esc_hash_build(esc_ctx *ctx, const int32_t *dev_keys, int64_t nkeys, void *d
  * over probe rows i of the product over j of the number of build rows of
  * table j whose key equals probe column key_cols[j] at row i (int32 or
  * date32 columns).  Waits for the result.  The product of one row must fit
- * in 64 bits.  The count is reduced in a workspace of at least
- * esc_workspace_size(probe, ESC_WS_COUNT, ...) bytes (256-byte aligned, any
- * contents).  Errors: ESC_ERR_INVALID, ESC_ERR_TYPE (a float32 key column),
+ * in 64 bits.  dev_ws: a workspace of at least esc_workspace_size(probe,
+ * ESC_WS_COUNT, ...) bytes (256-byte aligned, any contents; checked but not
+ * written: the blocks' sums go to pinned host memory).  Errors: ESC_ERR_INVALID, ESC_ERR_TYPE (a float32 key column),
  * ESC_ERR_ALIGN / ESC_ERR_OOM (workspace). */
 int esc_join_count(esc_ctx *ctx, const esc_table *probe, const int32_t *key_cols, void *const *dev_tables,
                    const size_t *table_bytes, int ntables, void *dev_ws, size_t ws_bytes, void *stream,
