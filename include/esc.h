@@ -136,7 +136,8 @@ int esc_abi_version(void);
  *   ESC_BLOCKS_PER_CU n      count grid = n blocks per CU (default: occupancy);
  *   ESC_MAT_BLOCKS_PER_CU n  same for the materialization's write pass;
  *   ESC_NONTEMPORAL 0|1      non-temporal column loads;
- *   ESC_DENSE_SHIFT 0..12    write-pass dense threshold 2^-shift (default 7).
+ *   ESC_DENSE_SHIFT 0..12    density 2^-shift (default 7) from which the policy's
+ *                            cost model prices projected columns as read whole.
  * Outside the context: ESC_IN_HASH_MIN (compiler: smallest IN-list given a
  * slot table or bitmap, default 3, 0 = never) and ESC_AUTOTUNE_CACHE (a file
  * that keeps batched autotuning results between processes). */
@@ -144,9 +145,10 @@ int esc_ctx_create(int device, esc_ctx **out);
 int esc_ctx_destroy(esc_ctx *ctx);
 /* Number of compute units of the context's device. */
 int esc_ctx_num_cus(const esc_ctx *ctx, int *out);
-/* Fraction of a wave tile's rows that must qualify for the materialization
- * to read the tile's projected columns whole rather than gather them
- * (1/128 unless ESC_DENSE_SHIFT sets another power of two). */
+/* Fraction of a wave tile's rows from which the cost model prices a
+ * materialization's projected columns as read whole rather than gathered (1/128
+ * unless ESC_DENSE_SHIFT sets another power of two; the write pass itself
+ * reads only the sectors that hold qualifying rows at any density). */
 int esc_ctx_dense_fraction(const esc_ctx *ctx, double *out);
 
 /* ------------------------------------------------------------------ tables

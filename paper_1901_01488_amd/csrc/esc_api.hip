@@ -471,18 +471,27 @@ static int materialize_launch(esc_ctx *ctx, const esc_table *t, const esc_pred *
         // pass 1: per-wave-tile counts and lane masks, unless the preceding
         // count left them (then the launch only checks the workspace's stamp)
         if ((rc = count_launch(ctx, t, p, dev_ws, ws_bytes, s, &h->result, true, expect))) return rc;
-        // pass 2: offsets in row order (total in h->result and dev_total)
-        launch_scan(tiles, L.ntiles, offsets, h, dev_total != &h->result ? dev_total : nullptr, s);
+        // pass 2: offsets in row order (total in h->result and dev_total), by
+        // the write pass itself for few tiles
+        const bool own = capacity > 0 && L.ntiles <= kOwnPrefixTiles;
+        unsigned long long *const total = dev_total != &h->result ? dev_total : nullptr;
+        if (!own) launch_scan(tiles, L.ntiles, offsets, h, total, s);
         // pass 3: write
         if (capacity > 0) {
             WriteFn fn = write_fn(rpt);
-            const int occ = occupancy((const void *)fn, kScanBlock, 0);
-            int64_t grid = (int64_t)ctx->num_cus * (ctx->mat_bpc > 0 ? std::min(ctx->mat_bpc, occ) : occ);
-            const int64_t blocks_needed = (L.ntiles + kScanBlock / 64 - 1) / (kScanBlock / 64);
-            if (grid > blocks_needed) grid = blocks_needed;
-            const uint32_t dense_min = std::max<uint32_t>(1u, (uint32_t)(64 * rpt) >> ctx->dense_shift);
-            hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(kScanBlock), 0, s, bits, offsets, t->nrows, pa,
-                               dev_rowids, (unsigned long long)capacity, dense_min);
+            // tiles of a block: one unit for each of its waves, up to eight
+            // as long as there are eight blocks for every CU
+            const int64_t least = kScanBlock / 64 * 1024 / (64 * (int64_t)rpt);
+            const int64_t tpb = std::max(least, std::min(8 * least, L.ntiles / (8 * (int64_t)ctx->num_cus) / least * least));
+            const int64_t blocks_needed = (L.ntiles + tpb - 1) / tpb;
+            int64_t grid = blocks_needed;
+            if (!own) {
+                const int occ = occupancy((const void *)fn, kScanBlock, 0);
+                grid = std::min(grid, (int64_t)ctx->num_cus * (ctx->mat_bpc > 0 ? std::min(ctx->mat_bpc, occ) : occ));
+            }
+            hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(kScanBlock), 0, s, bits, tiles,
+                               own ? nullptr : offsets, L.ntiles, (int)tpb, pa, dev_rowids, (unsigned long long)capacity,
+                               h, total);
         }
     }
     hipError_t e = hipGetLastError();
@@ -498,13 +507,11 @@ int esc_materialize(esc_ctx *ctx, const esc_table *t, const esc_pred *p, const i
     if (!out_count) return fail(ESC_ERR_INVALID, "null out_count");
     if (!ctx || !dev_ws || ws_bytes < sizeof(WsHeader)) return fail(ESC_ERR_INVALID, "null handle or workspace");
     hipStream_t s = (hipStream_t)stream;
-    WsHeader *h = (WsHeader *)dev_ws;
+    // the total goes straight into pinned host memory, as esc_count's does
     int rc = materialize_launch(ctx, t, p, proj_cols, nproj, dev_rowids, dev_proj_out, capacity, dev_ws, ws_bytes, s,
-                                &h->result);
+                                ctx->pinned_dev);
     if (rc) return rc;
     hipError_t e;
-    if ((e = hipMemcpyAsync(ctx->pinned, &h->result, 8, hipMemcpyDeviceToHost, s)) != hipSuccess)
-        return hip_fail(e, "hipMemcpyAsync");
     if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
     const unsigned long long total = ctx->pinned[0];
     *out_count = total;

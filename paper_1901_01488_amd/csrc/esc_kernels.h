@@ -63,8 +63,14 @@ struct WsHeader {
 static_assert(sizeof(WsHeader) == 64, "workspace header is 64 bytes");
 
 typedef void (*CountFn)(const Program, const ColPtrs, int64_t, WsHeader *, unsigned long long *, const TileOut);
-typedef void (*WriteFn)(const uint32_t *, const uint32_t *, int64_t, const ProjArgs, int32_t *, unsigned long long,
-                        uint32_t);
+typedef void (*WriteFn)(const uint32_t *, const uint32_t *, const uint32_t *, int64_t, int, const ProjArgs, int32_t *,
+                        unsigned long long, WsHeader *, unsigned long long *);
+// Tiles up to which every block of the write pass finds its own offset (the
+// sum of the counts before it: about 2,000 blocks read half of them each, from
+// their L2) and no scan is launched.  60M rows, 29,297 tiles: 235 us a star
+// selection with the scan, 227 without; the scan's time grows with the tiles,
+// the sums' with tiles times blocks, and they meet at about 50,000.
+constexpr int64_t kOwnPrefixTiles = 40960;
 
 CountFn count_fn(int nslots, int ninsn, int variant, bool udf, bool tiles);
 constexpr int kCompactRPT = 16;   // rows per lane of the single-pass compaction
