@@ -8,8 +8,6 @@
 #include <unistd.h>
 
 #include <algorithm>
-#include <atomic>
-#include <chrono>
 #include <map>
 #include <mutex>
 #include <new>
@@ -34,25 +32,6 @@ int set_device(int device)
 {
     hipError_t e = hipSetDevice(device);
     return e == hipSuccess ? ESC_OK : hip_fail(e, "hipSetDevice");
-}
-
-void expect_words(unsigned long long *words, int n)
-{
-    for (int i = 0; i < n; i++) ((volatile unsigned long long *)words)[i] = kNoWord;
-}
-
-bool wait_words(const unsigned long long *words, int n)
-{
-    const auto end = std::chrono::steady_clock::now() + std::chrono::microseconds(kWaitUs);
-    for (int i = 0; i < n;) {
-        for (int spin = 0; spin < 64 && i < n; spin++) {
-            if (((const volatile unsigned long long *)words)[i] != kNoWord) i++;
-            else __builtin_ia32_pause();
-        }
-        if (i < n && std::chrono::steady_clock::now() > end) return false;
-    }
-    std::atomic_thread_fence(std::memory_order_acquire);
-    return true;
 }
 
 static std::mutex g_occ_mu;
@@ -311,7 +290,7 @@ int esc_workspace_init(esc_ctx *ctx, void *dev_ws, size_t ws_bytes, void *stream
 // tiles) the kernel returns at once if the workspace's stamp equals it.
 static int count_launch(esc_ctx *ctx, const esc_table *t, const esc_pred *p, void *dev_ws, size_t ws_bytes,
                         hipStream_t s, unsigned long long *dev_out, bool need_tiles,
-                        unsigned long long expect = 0ull, bool *stores_tiles = nullptr)
+                        unsigned long long expect = 0ull)
 {
     int rc = check_scan_args(ctx, t, p, dev_ws, ws_bytes, sizeof(WsHeader));
     if (rc) return rc;
@@ -328,7 +307,6 @@ static int count_launch(esc_ctx *ctx, const esc_table *t, const esc_pred *p, voi
         // materialization reads back); otherwise the plain count's shape
         const WsLayout Lt = ws_layout(t->nrows, count_rpt(ctx->count_variant, P.nslots, P.ninsn, true));
         const bool tiles = ws_bytes >= Lt.bytes;
-        if (stores_tiles) *stores_tiles = tiles;
         if (!tiles && need_tiles) return fail(ESC_ERR_OOM, "workspace of %zu bytes, %zu needed", ws_bytes, Lt.bytes);
         const int rpt = count_rpt(ctx->count_variant, P.nslots, P.ninsn, tiles);
         const WsLayout L = ws_layout(t->nrows, rpt);
@@ -359,7 +337,9 @@ int esc_count(esc_ctx *ctx, const esc_table *t, const esc_pred *p, void *dev_ws,
     if (!out_count) return fail(ESC_ERR_INVALID, "null out_count");
     hipStream_t s = (hipStream_t)stream;
     // the kernel's last block writes the count straight into pinned host
-    // memory: no copy command between the kernel and the wait
+    // memory: no copy command between the kernel and the wait (waiting for
+    // the word to change instead of synchronizing the stream measured slower:
+    // 33.7 against 24.1 us per call on a 1M-row table)
     int rc = check_scan_args(ctx, t, p, dev_ws, ws_bytes, sizeof(WsHeader));
     if (rc) return rc;
     // a predicate the compiler decided (always true or false) or an empty
@@ -369,16 +349,10 @@ int esc_count(esc_ctx *ctx, const esc_table *t, const esc_pred *p, void *dev_ws,
         *out_count = (pf & P_ALWAYS_TRUE) ? (uint64_t)t->nrows : 0u;
         return ESC_OK;
     }
-    bool tiles = false;
-    expect_words(ctx->pinned, 1);
-    if ((rc = count_launch(ctx, t, p, dev_ws, ws_bytes, s, ctx->pinned_dev, false, 0ull, &tiles))) return rc;
-    // tiles left for a materialization, perhaps on another stream, need the
-    // whole kernel; a plain count leaves only the word
-    if (tiles || !wait_words(ctx->pinned, 1)) {
-        const hipError_t e = hipStreamSynchronize(s);
-        if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
-    }
-    *out_count = *(volatile unsigned long long *)ctx->pinned;
+    if ((rc = count_launch(ctx, t, p, dev_ws, ws_bytes, s, ctx->pinned_dev, false))) return rc;
+    hipError_t e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
+    *out_count = ctx->pinned[0];
     return ESC_OK;
 }
 

@@ -95,16 +95,13 @@ __global__ __launch_bounds__(kScanBlock) void count_kernel(const Program P, cons
         // value left by the previous ones, so the block whose RMW returns
         // gridDim.x - 1 blocks done has read the sum of every other block:
         // exact without fences and without any order between two
-        // addresses.  That block resets the word, so the next launch on the
-        // workspace starts from zero, and then publishes the total: the host
-        // may act on it before the kernel ends (the word that the reset takes
-        // out equals `all`; adding their difference makes the store wait).
-        const unsigned long long mine = (1ull << kTotalBits) | b;
-        const unsigned long long all = atomicAdd(&ws->total, mine) + mine;
-        if ((all >> kTotalBits) == gridDim.x) {
+        // addresses.  That block publishes the total and resets the word,
+        // so the next launch on the workspace starts from zero.
+        const unsigned long long old = atomicAdd(&ws->total, (1ull << kTotalBits) | b);
+        if ((old >> kTotalBits) == gridDim.x - 1u) {
+            *out = (old & ((1ull << kTotalBits) - 1ull)) + b;
+            atomicExch(&ws->total, 0ull);
             if (TILES) ws->stamp = to.stamp;
-            const unsigned long long was = atomicExch(&ws->total, 0ull);
-            store_host_word(out, (all & ((1ull << kTotalBits) - 1ull)) + (was - all));
         }
     }
 }

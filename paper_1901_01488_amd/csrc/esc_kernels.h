@@ -49,13 +49,6 @@ struct TileOut {
     unsigned long long expect;
 };
 
-// One result word in pinned host memory, visible to the host at once (not
-// with the end of the kernel).
-__device__ __forceinline__ void store_host_word(unsigned long long *p, unsigned long long v)
-{
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
 // The count's running word: rows in bits 0..kTotalBits-1, blocks done above
 // (a table has fewer than 2^31 rows, a grid fewer than 2^24 blocks).
 constexpr int kTotalBits = 40;

@@ -32,17 +32,6 @@ int hip_fail(hipError_t e, const char *what);
 // Makes `device` current; on failure clears HIP's sticky error and reports it.
 int set_device(int device);
 int occupancy(const void *fn, int block, int dyn_lds);
-// Results that a kernel stores in pinned host words with store_host_word:
-// expect_words marks n of them as not yet there, before the launch, and
-// wait_words waits for all of them (false after kWaitUs without them: the
-// caller then synchronizes the stream, which also reports a failed kernel).
-// A count on 1M rows takes 16.4 us this way, 21.7 by synchronizing the stream.
-// Only for kernels that leave nothing else behind: their other stores are
-// visible to other streams only once the kernel has ended.
-constexpr unsigned long long kNoWord = ~0ull;
-constexpr int kWaitUs = 2000;
-void expect_words(unsigned long long *words, int n);
-bool wait_words(const unsigned long long *words, int n);
 ColPtrs slot_ptrs(const esc_table *t, const Program &P, int nt);
 
 }  // namespace esc
