@@ -200,7 +200,7 @@ int esc_ctx_create(int device, esc_ctx **out)
     hipDeviceProp_t prop;
     if ((e = hipGetDeviceProperties(&prop, device)) != hipSuccess) { delete c; return hip_fail(e, "hipGetDeviceProperties"); }
     c->num_cus = prop.multiProcessorCount;
-    if ((e = hipHostMalloc((void **)&c->pinned, 4096, hipHostMallocDefault)) != hipSuccess) {
+    if ((e = hipHostMalloc((void **)&c->pinned, kPinnedBytes, hipHostMallocDefault)) != hipSuccess) {
         delete c;
         return hip_fail(e, "hipHostMalloc");
     }
@@ -288,9 +288,11 @@ int esc_workspace_init(esc_ctx *ctx, void *dev_ws, size_t ws_bytes, void *stream
 // when it has room for them (and remembers for which table and predicate).
 // With expect != 0 (only when the workspace should hold this predicate's
 // tiles) the kernel returns at once if the workspace's stamp equals it.
+// host_words (a caller that passes the context's pinned words as dev_out):
+// receives the number of words whose sum is the count.
 static int count_launch(esc_ctx *ctx, const esc_table *t, const esc_pred *p, void *dev_ws, size_t ws_bytes,
                         hipStream_t s, unsigned long long *dev_out, bool need_tiles,
-                        unsigned long long expect = 0ull)
+                        unsigned long long expect = 0ull, int *host_words = nullptr)
 {
     int rc = check_scan_args(ctx, t, p, dev_ws, ws_bytes, sizeof(WsHeader));
     if (rc) return rc;
@@ -305,24 +307,33 @@ static int count_launch(esc_ctx *ctx, const esc_table *t, const esc_pred *p, voi
     } else {
         // a workspace with room for the tiles receives them (the shape a
         // materialization reads back); otherwise the plain count's shape
-        const WsLayout Lt = ws_layout(t->nrows, count_rpt(ctx->count_variant, P.nslots, P.ninsn, true));
+        const WsLayout Lt = ws_layout(t->nrows, count_rpt(ctx->count_variant, P.nslots, P.ninsn, true, t->nrows, ctx->num_cus));
         const bool tiles = ws_bytes >= Lt.bytes;
         if (!tiles && need_tiles) return fail(ESC_ERR_OOM, "workspace of %zu bytes, %zu needed", ws_bytes, Lt.bytes);
-        const int rpt = count_rpt(ctx->count_variant, P.nslots, P.ninsn, tiles);
+        const int rpt = count_rpt(ctx->count_variant, P.nslots, P.ninsn, tiles, t->nrows, ctx->num_cus);
         const WsLayout L = ws_layout(t->nrows, rpt);
-        TileOut to{nullptr, nullptr, 0ull, 0ull};
+        TileOut to{nullptr, nullptr, 0ull, 0ull, 0};
         if (tiles) {
             to.counts = (uint32_t *)((char *)dev_ws + L.counts_off);
             to.bits = (uint32_t *)((char *)dev_ws + L.bits_off);
             to.expect = expect;
             to.stamp = expect ? expect : new_stamp();
         }
-        CountFn fn = count_fn(P.nslots, P.ninsn, ctx->count_variant, (P.flags & P_HAS_UDF) != 0, tiles);
+        CountFn fn = count_fn(P.nslots, rpt, (P.flags & P_HAS_UDF) != 0, tiles);
         const int occ = occupancy((const void *)fn, kScanBlock, 0);
         int64_t grid = (int64_t)ctx->num_cus *
                        (ctx->bpc > 0 ? count_bpc(ctx->count_variant, P.nslots, ctx->bpc, tiles) : occ);
         const int64_t blocks_needed = (L.ntiles + kScanBlock / 64 - 1) / (kScanBlock / 64);
+        // long programs on tables of up to two blocks per CU run them all at
+        // once (2.2M rows of the Section 1 selection: 28.6 us in two rounds, 23.5)
+        if (!tiles && P.ninsn > P.nslots && blocks_needed <= 2 * (int64_t)ctx->num_cus) grid = blocks_needed;
         if (grid > blocks_needed) grid = blocks_needed;
+        // a blocking count whose blocks each take one round gets a word of
+        // each; on longer ones the atomics of the blocks' ends spread out
+        if (host_words && !tiles && grid == blocks_needed && grid <= kSlotWord) {
+            to.parts = 1;
+            *host_words = (int)grid;
+        }
         hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(kScanBlock), to.counts ? kTileBufBytes : 0, s, P,
                            slot_ptrs(t, P, ctx->nt), t->nrows, (WsHeader *)dev_ws, dev_out, to);
         if (to.counts) remember_tiles(ctx, dev_ws, t, p, rpt, to.stamp);
@@ -338,8 +349,9 @@ int esc_count(esc_ctx *ctx, const esc_table *t, const esc_pred *p, void *dev_ws,
     hipStream_t s = (hipStream_t)stream;
     // the kernel's last block writes the count straight into pinned host
     // memory: no copy command between the kernel and the wait (waiting for
-    // the word to change instead of synchronizing the stream measured slower:
-    // 33.7 against 24.1 us per call on a 1M-row table)
+    // the word to change instead of synchronizing the stream returns 5 us
+    // sooner on a 1M-row table and makes the next synchronization of the
+    // device 9 to 17 us longer, which retires the kernel in its place)
     int rc = check_scan_args(ctx, t, p, dev_ws, ws_bytes, sizeof(WsHeader));
     if (rc) return rc;
     // a predicate the compiler decided (always true or false) or an empty
@@ -349,10 +361,13 @@ int esc_count(esc_ctx *ctx, const esc_table *t, const esc_pred *p, void *dev_ws,
         *out_count = (pf & P_ALWAYS_TRUE) ? (uint64_t)t->nrows : 0u;
         return ESC_OK;
     }
-    if ((rc = count_launch(ctx, t, p, dev_ws, ws_bytes, s, ctx->pinned_dev, false))) return rc;
+    int words = 1;
+    if ((rc = count_launch(ctx, t, p, dev_ws, ws_bytes, s, ctx->pinned_dev, false, 0ull, &words))) return rc;
     hipError_t e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
-    *out_count = ctx->pinned[0];
+    uint64_t total = 0;
+    for (int i = 0; i < words; i++) total += ctx->pinned[i];
+    *out_count = total;
     return ESC_OK;
 }
 
@@ -413,7 +428,7 @@ static int materialize_launch(esc_ctx *ctx, const esc_table *t, const esc_pred *
                               void *dev_ws, size_t ws_bytes, hipStream_t s, unsigned long long *dev_total)
 {
     if (!ctx || !t || !p) return fail(ESC_ERR_INVALID, "null handle");
-    const int rpt = count_rpt(ctx->count_variant, p->prog.nslots, p->prog.ninsn, true);
+    const int rpt = count_rpt(ctx->count_variant, p->prog.nslots, p->prog.ninsn, true, t->nrows, ctx->num_cus);
     const WsLayout L = ws_layout(t->nrows, rpt);
     int rc = check_scan_args(ctx, t, p, dev_ws, ws_bytes, L.bytes);
     if (rc) return rc;
@@ -600,7 +615,7 @@ int esc_materialize_noalloc(esc_ctx *ctx, const esc_table *t, const esc_pred *p,
     if (!dev_count) return fail(ESC_ERR_INVALID, "null dev_count");
     if (!ctx || !t || !p) return fail(ESC_ERR_INVALID, "null handle");
     if (!ctx->scratch) return fail(ESC_ERR_INVALID, "context has no static scratch");
-    const WsLayout L = ws_layout(t->nrows, count_rpt(ctx->count_variant, p->prog.nslots, p->prog.ninsn, true));
+    const WsLayout L = ws_layout(t->nrows, count_rpt(ctx->count_variant, p->prog.nslots, p->prog.ninsn, true, t->nrows, ctx->num_cus));
     if (L.bytes > kStaticScratchBytes)
         return fail(ESC_ERR_CAPACITY, "%lld rows need %zu bytes of scratch, the static scratch holds %zu",
                     (long long)t->nrows, L.bytes, kStaticScratchBytes);

@@ -88,6 +88,12 @@ __global__ __launch_bounds__(kScanBlock) void count_kernel(const Program P, cons
     if (threadIdx.x == 0) {
         unsigned long long b = 0;
         for (int w = 0; w < NW; w++) b += s_cnt[w];
+        if (!TILES && to.parts) {
+            // every block has a host word of its own, which the host adds
+            // up: no chain of atomics on one word (about 10 ns a block)
+            out[blockIdx.x] = b;
+            return;
+        }
         // One 64-bit word carries both the running row count (low
         // kTotalBits bits) and the number of blocks done (high bits), so
         // each block's contribution is one atomic read-modify-write of one
@@ -173,7 +179,7 @@ constexpr CountFn count_table_impl(int k, std::integer_sequence<int, Ks...>)
 // 4.8); counts that store tiles with 16 rows per lane store twice the mask
 // bytes and give the offset scan twice the tiles (154 against 145 us per
 // count).
-int count_rpt(int variant, int k, int ninsn, bool tiles)
+static int rows_per_lane(int variant, int k, int ninsn, bool tiles)
 {
     if (variant == 2 && !tiles) return 8;
     if (variant == 3 && !tiles) return k <= 2 ? 32 : 16;
@@ -188,6 +194,23 @@ int count_rpt(int variant, int k, int ninsn, bool tiles)
     return variant == 0 || k > (tiles && variant == 4 ? 6 : 4) ? 16 : 32;
 }
 
+// Plain counts of tables of few tiles take fewer rows per lane (variant 4),
+// down to 8, while there are fewer than two tiles a CU: a wave's time is then
+// the call's, and it interprets its program on all of its rows.  The Section 1
+// selection with its udf on 100,000 rows 21.9 -> 17.9 us, 700,000 22.1 ->
+// 19.0, 1M 21.5 -> 19.0, most of it of this rule.  With the line at 1.5 tiles
+// a CU 1M rows stay at 21.1; at 3, 700,000 rows of the star table run in two
+// rounds (eight selections 150 us, 136 here).  Counts that store tiles keep
+// theirs: eight selections of 100,000 rows 184 us, 193 with half the rows per
+// lane.
+int count_rpt(int variant, int k, int ninsn, bool tiles, int64_t nrows, int cus)
+{
+    int rpt = rows_per_lane(variant, k, ninsn, tiles);
+    if (variant != 4 || tiles) return rpt;
+    while (rpt > 8 && (nrows + 64 * rpt - 1) / (64 * rpt) < 2 * (int64_t)cus) rpt /= 2;
+    return rpt;
+}
+
 // blocks of four waves per CU; one-column counts run two to keep enough
 // loads in flight (variant 3: plain counts only; variant 4: also counts
 // that store tiles)
@@ -197,16 +220,16 @@ int count_bpc(int variant, int k, int bpc, bool tiles)
     return 2 * bpc;
 }
 
-CountFn count_fn(int k, int ninsn, int variant, bool udf, bool tiles)
+CountFn count_fn(int k, int rpt, bool udf, bool tiles)
 {
     using S = std::make_integer_sequence<int, kMaxSlots + 1>;
     // counts that store tiles run 16 or 32 rows per lane (count_rpt)
     if (tiles) {
-        if (count_rpt(variant, k, ninsn, true) == 16)
+        if (rpt == 16)
             return udf ? count_table_impl<16, true, true>(k, S{}) : count_table_impl<16, false, true>(k, S{});
         return udf ? count_table_impl<32, true, true>(k, S{}) : count_table_impl<32, false, true>(k, S{});
     }
-    switch (count_rpt(variant, k, ninsn, false)) {
+    switch (rpt) {
     case 8: return udf ? count_table_impl<8, true, false>(k, S{}) : count_table_impl<8, false, false>(k, S{});
     case 16: return udf ? count_table_impl<16, true, false>(k, S{}) : count_table_impl<16, false, false>(k, S{});
     default: return udf ? count_table_impl<32, true, false>(k, S{}) : count_table_impl<32, false, false>(k, S{});

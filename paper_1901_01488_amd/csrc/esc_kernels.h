@@ -47,6 +47,7 @@ struct TileOut {
     uint32_t *bits;
     unsigned long long stamp;
     unsigned long long expect;
+    int32_t parts;   // plain counts: out holds one host word per block
 };
 
 // The count's running word: rows in bits 0..kTotalBits-1, blocks done above
@@ -72,13 +73,13 @@ typedef void (*WriteFn)(const uint32_t *, const uint32_t *, const uint32_t *, in
 // the sums' with tiles times blocks, and they meet at about 50,000.
 constexpr int64_t kOwnPrefixTiles = 40960;
 
-CountFn count_fn(int nslots, int ninsn, int variant, bool udf, bool tiles);
+CountFn count_fn(int nslots, int rpt, bool udf, bool tiles);
 constexpr int kCompactRPT = 16;   // rows per lane of the single-pass compaction
 typedef void (*CompactFn)(const Program, const ColPtrs, int64_t, unsigned long long *, unsigned int *,
                           const ProjArgs, const ProjSlots, int32_t *, unsigned long long, uint32_t,
                           unsigned long long *);
 CompactFn compact_fn(int nslots, bool udf);
-int count_rpt(int variant, int nslots, int ninsn, bool tiles);
+int count_rpt(int variant, int nslots, int ninsn, bool tiles, int64_t nrows, int cus);
 int count_bpc(int variant, int nslots, int bpc, bool tiles);
 WriteFn write_fn(int rpt);
 typedef void (*ConjFn)(const Program *, int, const ColPtrs, int64_t, unsigned long long *);

@@ -8,7 +8,7 @@
 struct esc_ctx {
     int device = 0;
     int num_cus = 0;
-    unsigned long long *pinned = nullptr;   // 4 KiB of pinned host memory for read-backs
+    unsigned long long *pinned = nullptr;   // kPinnedBytes of pinned host memory for read-backs
     unsigned long long *pinned_dev = nullptr;   // the same memory as the device addresses it
     int count_variant = 4;                  // count kernel shape (see count_rpt / count_bpc)
     int nt = 1;                             // streaming loads in the scans
@@ -23,8 +23,9 @@ struct esc_ctx {
 
 // words of the pinned block: [0, kSlotWord) read-backs of the blocking calls,
 // then one word per esc_count_begin slot
-constexpr int kSlotWord = 256;
-static_assert(kSlotWord + ESC_COUNT_SLOTS <= 512, "the slots fit the 4 KiB pinned block");
+constexpr int kSlotWord = 512;
+constexpr int kPinnedBytes = 8192;
+static_assert((kSlotWord + ESC_COUNT_SLOTS) * 8 <= kPinnedBytes, "the slots fit the pinned block");
 
 namespace esc {
 
