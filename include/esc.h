@@ -204,7 +204,7 @@ int esc_pred_get_info(const esc_pred *p, esc_pred_info *out);
  * rows and the per-row truth values as bit masks.  kind: ESC_WS_COUNT
  * (esc_count, esc_join_count: 256 bytes), ESC_WS_MATERIALIZE
  * (esc_materialize; also serves esc_count), ESC_WS_CONJUNCTS
- * (esc_count_conjuncts: the conjunct programs and counters). */
+ * (esc_count_conjuncts: the conjunct programs). */
 #define ESC_WS_COUNT 0
 #define ESC_WS_MATERIALIZE 1
 #define ESC_WS_CONJUNCTS 2

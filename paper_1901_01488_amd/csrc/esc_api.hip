@@ -256,9 +256,9 @@ int esc_ctx_dense_fraction(const esc_ctx *ctx, double *out)
     return ESC_OK;
 }
 
-// split selectivities: the conjunct programs, then 2 * kMaxConj counters
-constexpr size_t kConjCountersOff = ((size_t)kMaxConj * sizeof(Program) + 255) & ~(size_t)255;
-constexpr size_t kConjWsBytes = kConjCountersOff + 2 * kMaxConj * sizeof(unsigned long long);
+// split selectivities: room for the conjunct programs that do not fit a
+// ConjPack, and 512 bytes that callers have always given
+constexpr size_t kConjWsBytes = (((size_t)kMaxConj * sizeof(Program) + 255) & ~(size_t)255) + 512;
 
 int esc_workspace_size(const esc_table *t, int kind, size_t *bytes)
 {
@@ -330,7 +330,7 @@ static int count_launch(esc_ctx *ctx, const esc_table *t, const esc_pred *p, voi
         if (grid > blocks_needed) grid = blocks_needed;
         // a blocking count whose blocks each take one round gets a word of
         // each; on longer ones the atomics of the blocks' ends spread out
-        if (host_words && !tiles && grid == blocks_needed && grid <= kSlotWord) {
+        if (host_words && !tiles && grid == blocks_needed && grid <= kCountParts) {
             to.parts = 1;
             *host_words = (int)grid;
         }
@@ -568,33 +568,40 @@ int esc_count_conjuncts(esc_ctx *ctx, const esc_table *t, const esc_pred *p, voi
     if ((rc = set_device(ctx->device))) return rc;
     hipError_t e;
     hipStream_t s = (hipStream_t)stream;
-    Program *d_progs = (Program *)dev_ws;
-    unsigned long long *d_out = (unsigned long long *)((char *)dev_ws + kConjCountersOff);
-    if ((e = hipMemcpyAsync(d_progs, progs.data(), m * sizeof(Program), hipMemcpyHostToDevice, s)) != hipSuccess)
-        return hip_fail(e, "upload conjunct programs");
-    launch_zero(d_out, 2 * kMaxConj, s);
-    bool udf = false;
-    for (const Program &q : progs) udf |= (q.flags & P_HAS_UDF) != 0;
+    int64_t grid = 0;
     if (t->nrows > 0) {
+        // programs that fit go as a kernel argument: no upload before the
+        // kernel (10,000 rows 28 us a call with it, the counters' clearing
+        // and their copy back, 22 without)
+        ConjPack pack;
+        const bool packed = pack_conjuncts(progs, pack);
+        const Program *d_progs = (const Program *)dev_ws;
+        if (!packed && (e = hipMemcpyAsync(dev_ws, progs.data(), m * sizeof(Program), hipMemcpyHostToDevice, s)) != hipSuccess)
+            return hip_fail(e, "upload conjunct programs");
+        bool udf = false;
+        for (const Program &q : progs) udf |= (q.flags & P_HAS_UDF) != 0;
         ColPtrs cp{};
         cp.nt = ctx->nt;
         for (int c = 0; c < nslots; c++) cp.p[c] = (const uint32_t *)t->cols[slot_col[c]];
-        ConjFn fn = conj_fn(nslots, udf);
-        const int occ = occupancy((const void *)fn, kScanBlock, 0);
-        int64_t grid = (int64_t)ctx->num_cus * occ;
+        ConjFn fn = conj_fn(nslots, udf, packed);
+        const int lds = m * kScanBlock * (int)sizeof(unsigned long long);
+        // two blocks a CU: 40M star rows take 313 us for four predicates, 334
+        // with one and 321 to 330 with four to eight (10M: 144, 152, 146 to 153)
+        grid = std::min(2 * (int64_t)ctx->num_cus, (int64_t)(kSlotWord / m));
         const int64_t blocks_needed = (t->nrows + 16 * kScanBlock - 1) / (16 * kScanBlock);
         if (grid > blocks_needed) grid = blocks_needed;
-        hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(kScanBlock), 0, s, d_progs, m, cp, t->nrows, d_out);
+        hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(kScanBlock), lds, s, pack, d_progs, m, cp, t->nrows,
+                           ctx->pinned_dev);
+        if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "conjunct kernel launch");
     }
-    if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "conjunct kernel launch");
-    if ((e = hipMemcpyAsync(ctx->pinned, d_out, 2 * kMaxConj * sizeof(unsigned long long), hipMemcpyDeviceToHost,
-                            s)) != hipSuccess)
-        return hip_fail(e, "hipMemcpyAsync");
     if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
-    for (int i = 0; i < m; i++) {
-        conj_counts[i] = ctx->pinned[i];
-        prefix_counts[i] = ctx->pinned[kMaxConj + i];
-    }
+    for (int i = 0; i < m; i++) conj_counts[i] = prefix_counts[i] = 0;
+    const unsigned long long *part = ctx->pinned;
+    for (int64_t b = 0; b < grid; b++, part += m)
+        for (int i = 0; i < m; i++) {
+            conj_counts[i] += (uint32_t)part[i];
+            prefix_counts[i] += part[i] >> 32;
+        }
     *out_nconj = m;
     return ESC_OK;
 }

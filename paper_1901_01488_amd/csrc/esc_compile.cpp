@@ -839,6 +839,42 @@ int split_conjuncts(const esc_pred *p, std::vector<Program> &out, int &nslots, i
     return ESC_OK;
 }
 
+static_assert(kMaxConjParts == ESC_MAX_CONJ, "one part per conjunct");
+
+bool pack_conjuncts(const std::vector<Program> &progs, ConjPack &pack)
+{
+    int ninsn = 0, ntables = 0, nk = 0;
+    for (const Program &P : progs) {
+        ninsn += P.ninsn;
+        ntables += P.ntables;
+        nk += P.nk;
+    }
+    if (ninsn > kMaxInsns || ntables > kMaxTables || nk > kMaxKpool) return false;
+    pack.ntables = ntables;
+    int insn = 0, table = 0, list = ntables * kSlotTable;
+    for (size_t i = 0; i < progs.size(); i++) {
+        const Program &P = progs[i];
+        const int words = P.ntables * kSlotTable;
+        std::copy(P.kpool, P.kpool + words, pack.kpool + table * kSlotTable);
+        std::copy(P.kpool + words, P.kpool + P.nk, pack.kpool + list);
+        pack.first[i] = insn;
+        for (int k = 0; k < P.ninsn; k++) {
+            Insn I = P.insn[k];
+            if (I.op == T_IN_HASH || I.op == T_IN_BITMAP) {
+                I.c += table;
+                I.a += table * kSlotTable;
+            } else if (I.op == T_IN_I32 || I.op == T_IN_F32) {
+                I.a += list - words;
+            }
+            pack.insn[insn++] = I;
+        }
+        table += P.ntables;
+        list += P.nk - words;
+    }
+    pack.first[progs.size()] = insn;
+    return true;
+}
+
 }  // namespace esc
 
 // ---------------------------------------------------------------- C ABI

@@ -84,8 +84,8 @@ struct SlotTabs {
     static_assert(NT == 0 || NT == 4, "four slot tables per program");
 };
 
-template <int NT>
-__device__ __forceinline__ SlotTabs<NT> load_tables(const Program &P)
+template <int NT, typename Prog>
+__device__ __forceinline__ SlotTabs<NT> load_tables(const Prog &P)
 {
     SlotTabs<NT> t;
     if constexpr (NT > 0) {
@@ -259,8 +259,8 @@ __device__ __forceinline__ void run_udf(const Insn &I, const uint32_t (&v)[KK][R
     }
 }
 
-template <int K, int RPT, bool UDF, int NT, int KK = (K > 0 ? K : 1)>
-__device__ __forceinline__ uint32_t run_program_tree(const Program &P, const uint32_t (&v)[KK][RPT], uint32_t valid,
+template <int K, int RPT, bool UDF, int NT, typename Prog, int KK = (K > 0 ? K : 1)>
+__device__ __forceinline__ uint32_t run_program_tree(const Prog &P, const uint32_t (&v)[KK][RPT], uint32_t valid,
                                                      const SlotTabs<NT> &tabs)
 {
     uint32_t acc = valid, cm = 0;
@@ -305,9 +305,9 @@ __device__ __forceinline__ uint32_t run_program_tree(const Program &P, const uin
 // not reserve registers for the udf accumulator).  TREE = true dispatches
 // on the slot with a switch and tests for the common int range first (the
 // batched kernel, whose wave streams are dominated by the interpreter's
-// scalar branches).
-template <int K, int RPT, bool UDF = true, int NT = 0, bool TREE = false, int KK = (K > 0 ? K : 1)>
-__device__ __forceinline__ uint32_t run_program(const Program &P, const uint32_t (&v)[KK][RPT], uint32_t valid,
+// scalar branches).  Prog has a Program's ninsn, insn and kpool.
+template <int K, int RPT, bool UDF = true, int NT = 0, bool TREE = false, typename Prog, int KK = (K > 0 ? K : 1)>
+__device__ __forceinline__ uint32_t run_program(const Prog &P, const uint32_t (&v)[KK][RPT], uint32_t valid,
                                                 const SlotTabs<NT> &tabs = SlotTabs<NT>{})
 {
     if constexpr (TREE) return run_program_tree<K, RPT, UDF, NT>(P, v, valid, tabs);

@@ -45,5 +45,8 @@ int compile(const esc_table *schema, const esc_node *nodes, int nnodes,
 // otherwise), each compiled on its own, with their column slots mapped onto
 // one common slot order (nslots, slot_col).
 int split_conjuncts(const esc_pred *p, std::vector<Program> &out, int &nslots, int *slot_col);
+// The programs as one list with one pool; false if they need more
+// instructions, pool words or slot tables than it holds.
+bool pack_conjuncts(const std::vector<Program> &progs, ConjPack &pack);
 
 }  // namespace esc

@@ -82,8 +82,8 @@ CompactFn compact_fn(int nslots, bool udf);
 int count_rpt(int variant, int nslots, int ninsn, bool tiles, int64_t nrows, int cus);
 int count_bpc(int variant, int nslots, int bpc, bool tiles);
 WriteFn write_fn(int rpt);
-typedef void (*ConjFn)(const Program *, int, const ColPtrs, int64_t, unsigned long long *);
-ConjFn conj_fn(int nslots, bool udf);
+typedef void (*ConjFn)(const ConjPack, const Program *, int, const ColPtrs, int64_t, unsigned long long *);
+ConjFn conj_fn(int nslots, bool udf, bool packed);
 void launch_zero(unsigned long long *p, int64_t nwords, hipStream_t s);
 // offsets of m tile counts in row order; the total goes to ws->result and,
 // when total is not null, to *total

@@ -66,4 +66,22 @@ struct Program {
     uint32_t kpool[kMaxKpool];
 };
 
+// Instructions and pool of one program of several kept together.
+struct ProgView {
+    int32_t ninsn;
+    const Insn *insn;
+    const uint32_t *kpool;
+};
+
+// The programs of a split conjunction as one kernel argument (2 KiB of the 4
+// that a launch may pass): conjunct i is insn[first[i] .. first[i + 1]), and
+// all share one pool, its slot tables at kpool[0 .. 64 * ntables).
+constexpr int kMaxConjParts = 32;
+struct ConjPack {
+    int32_t ntables;
+    int32_t first[kMaxConjParts + 1];
+    Insn insn[kMaxInsns];
+    uint32_t kpool[kMaxKpool];
+};
+
 }  // namespace esc

@@ -23,9 +23,9 @@ struct esc_ctx {
 
 // words of the pinned block: [0, kSlotWord) read-backs of the blocking calls,
 // then one word per esc_count_begin slot
-constexpr int kSlotWord = 512;
-constexpr int kPinnedBytes = 8192;
-static_assert((kSlotWord + ESC_COUNT_SLOTS) * 8 <= kPinnedBytes, "the slots fit the pinned block");
+constexpr int kCountParts = 512;                    // blocks of a count with words of their own
+constexpr int kSlotWord = kCountParts * ESC_MAX_CONJ;   // as many blocks' words of split selectivities
+constexpr int kPinnedBytes = (kSlotWord + ESC_COUNT_SLOTS) * 8;
 
 namespace esc {
 
