@@ -326,9 +326,7 @@ bool fills_chip(const esc_batch *b, int64_t nrows) { return nrows >= 16384ll * b
 int index_grid(const esc_batch *b) { return std::max(1, b->ctx->num_cus * kIndexBlocksPerCu); }
 
 // Takes the predicates of each table's members that a predicate index counts
-// more cheaply than the interpreter out of members and into the plan.  Groups
-// are formed in the order of the predicates' OR clauses, so that predicates
-// with as many of them share the extra record words.
+// more cheaply than the interpreter out of members and into the plan.
 // small: whether the rule for small tables may be used; true if it was.
 bool plan_index(const esc_batch *b, const esc_batch_opts &o, bool small, std::vector<std::vector<int>> &members,
                 Plan &plan)
@@ -347,7 +345,7 @@ bool plan_index(const esc_batch *b, const esc_batch_opts &o, bool small, std::ve
         std::vector<int> order, at;   // positions in mem
         for (int i = 0; i < (int)mem.size(); i++)
             if (src.preds[i].nor >= 0) order.push_back(i);
-        std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return src.preds[x].nor < src.preds[y].nor; });
+        index_order(src, order, (int)order.size() > gmax);
         std::vector<char> taken(mem.size(), 0);
         for (size_t i = 0; i < order.size();) {
             int n = (int)std::min<size_t>(gmax, order.size() - i);

@@ -198,6 +198,35 @@ void IndexSource::add(const Program &P, const int32_t *dtypes)
     }
 }
 
+void index_order(const IndexSource &src, std::vector<int> &order, bool by_columns)
+{
+    if (!by_columns) {
+        std::stable_sort(order.begin(), order.end(),
+                         [&](int x, int y) { return src.preds[x].nor < src.preds[y].nor; });
+        return;
+    }
+    int64_t width[64] = {};   // intervals by column
+    int bit[64], by_width[64];
+    for (int i : order)
+        for (int l = src.preds[i].l0; l < src.preds[i].l1; l++)
+            width[src.leaves[l].col] += 1 + src.leaves[l].i1 - src.leaves[l].i0;
+    for (int c = 0; c < 64; c++) by_width[c] = c;
+    std::stable_sort(by_width, by_width + 64, [&](int a, int b) { return width[a] > width[b]; });
+    for (int k = 0; k < 64; k++) bit[by_width[k]] = 63 - k;
+    struct Key { uint64_t rank; int nor, pred; };
+    std::vector<Key> keys;
+    keys.reserve(order.size());
+    for (int i : order) {
+        uint64_t r = 0;
+        for (int l = src.preds[i].l0; l < src.preds[i].l1; l++) r |= 1ull << bit[src.leaves[l].col];
+        for (int s = 1; s < 64; s *= 2) r ^= r >> s;   // position in Gray code
+        keys.push_back({r, src.preds[i].nor, i});
+    }
+    std::stable_sort(keys.begin(), keys.end(),
+                     [](const Key &a, const Key &b) { return a.nor != b.nor ? a.nor < b.nor : a.rank < b.rank; });
+    for (size_t k = 0; k < keys.size(); k++) order[k] = keys[k].pred;
+}
+
 bool build_index(const IndexSource &src, const int *member, int n, const int32_t *dtypes, IndexGroup &g,
                  std::vector<uint32_t> &blob)
 {

