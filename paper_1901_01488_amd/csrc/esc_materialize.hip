@@ -158,6 +158,14 @@ __device__ __forceinline__ void write_tile(uint32_t bits, int64_t base, unsigned
     }
 }
 
+// Orders a wave's LDS accesses before and after it.
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // The write pass works on units of 1,024 rows (16 per lane of the tile's
 // masks), one wave each.  The unit's qualifying rows are ranked in row order
 // and their places in the unit gathered in LDS; lane i then takes the i-th
@@ -166,20 +174,35 @@ __device__ __forceinline__ void write_tile(uint32_t bits, int64_t base, unsigned
 // read in ascending addresses, one sector after the other, only where a row
 // qualifies.  What bounds it is the latency of a unit's chain (offset, masks,
 // ranks, one read per column): values need no staging, so a wave keeps 12
-// reads per lane in flight in few registers and eight waves share a SIMD.
-// Staging each column's values in LDS, with whole 16-byte reads in dense
-// tiles, ran at five waves: 131 us for the temporary tables of the star
-// selections (60M rows, 0.9-8 % of them, three columns), against 81 us now;
-// 35 % of 20M rows take 73 us either way, the rate of a copy.
+// reads per lane in flight in few registers.  Staging each 256-row chunk of
+// a tile column by column took 131 us for the temporary tables of the star
+// selections (60M rows, 0.9-8 % of them, three columns), against 81 us now.
+//
+// Where many rows of a unit qualify, reading and writing a row a lane is the
+// bound: four times the instructions of whole 16-byte groups, each touching
+// lines that the next one shares.  A unit of kDenseRows and more reads each
+// column's groups, places the values in LDS by rank and writes aligned
+// 16-byte groups (the last tile's units, whose rows may end inside a group,
+// excepted).  Two materializations on 40M rows, one, three and four columns,
+// before / a row a lane throughout / now: 79 % of the rows 320, 544, 659 /
+// 358, 616, 804 / 275, 510, 584 us; 35 %: 235, 423, 513 / 240, 424, 528 /
+// 213, 391, 431.  The line at a quarter of the rows instead of an eighth costs
+// 18 to 22 % of them 3 to 10 % (200, 347, 402 against 195, 340, 366); below it
+// both ways meet.  The 89 registers of both ways together leave five waves a
+// SIMD: eight sparse selections on 6M rows take 316 us, 303 with the 48 of a
+// row a lane alone; held to 80 or 64 registers 316 and 324.
 constexpr int kUnitRows = 1024;
+constexpr uint32_t kDenseRows = kUnitRows / 8;
 
 template <int RPT>
 __device__ __forceinline__ void write_unit(uint32_t bits, int64_t base, unsigned long long p, const ProjArgs &pa,
-                                           int32_t *rowids, unsigned long long cap, uint16_t *place)
+                                           int32_t *rowids, unsigned long long cap, bool whole, uint32_t *buf)
 {
     constexpr int NJ = kUnitRows / (4 * kWave);   // chunks of 256 rows
     const int lane = lane_id();
+    uint16_t *place = (uint16_t *)buf;
     uint32_t n = 0;   // wave-uniform: rows so far
+    uint32_t first[NJ];   // rank of the lane's first qualifying row of each chunk
 #pragma unroll
     for (int j = 0; j < NJ; j++) {
         const uint32_t nib = (bits >> (4 * j)) & 0xfu;
@@ -192,16 +215,65 @@ __device__ __forceinline__ void write_unit(uint32_t bits, int64_t base, unsigned
             k = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, k));
             n += (uint32_t)__popcll(m);
         }
+        first[j] = k;
+    }
+    const uint32_t avail = (uint32_t)(p + n <= cap ? n : cap - p);
+    if (whole && n >= kDenseRows) {
+        // one column at a time: its values (or the row ids) to their ranks in
+        // LDS, then out in 16-byte groups; a run begins at word `head` of one
+        auto column = [&](const uint32_t *src, uint32_t *dst, bool ids) {
+            u32x4 v[NJ];
+            if (!ids) {
+#pragma unroll
+                for (int j = 0; j < NJ; j++)
+                    if ((bits >> (4 * j)) & 0xfu)
+                        v[j] = __builtin_nontemporal_load((const u32x4 *)(src + base + lane * 4 + j * 4 * kWave));
+            } else {
+#pragma unroll
+                for (int j = 0; j < NJ; j++)
+#pragma unroll
+                    for (int e = 0; e < 4; e++) v[j][e] = (uint32_t)base + lane * 4 + j * 4 * kWave + e;
+            }
+            const uint32_t head = (uint32_t)((uintptr_t)dst >> 2) & 3u, end = head + avail;
+#pragma unroll
+            for (int j = 0; j < NJ; j++) {
+                uint32_t k = head + first[j];
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
+                    const uint32_t on = (bits >> (4 * j + e)) & 1u;
+                    if (on) buf[k] = v[j][e];
+                    k += on;
+                }
+            }
+            wave_lds_fence();
+            for (uint32_t i = lane * 4; i < end; i += 4 * kWave) {
+                const u32x4 q = *(const u32x4 *)(buf + i);
+                if (i >= head && i + 4 <= end) {
+                    __builtin_nontemporal_store(q, (u32x4 *)(dst - head + i));
+                } else {
+#pragma unroll
+                    for (uint32_t e = 0; e < 4; e++)
+                        if (i + e >= head && i + e < end) dst[(int64_t)(i + e) - head] = q[e];
+                }
+            }
+            wave_lds_fence();
+        };
+        if (rowids) column(nullptr, (uint32_t *)rowids + p, true);
+#pragma unroll 1
+        for (int q = 0; q < pa.nproj; q++) column(pa.src[q], pa.dst[q] + p, false);
+        return;
+    }
+#pragma unroll
+    for (int j = 0; j < NJ; j++) {
+        uint32_t k = first[j];
 #pragma unroll
         for (int e = 0; e < 4; e++) {
-            if ((nib >> e) & 1u) place[k] = (uint16_t)(j * 256 + lane * 4 + e);
-            k += (nib >> e) & 1u;
+            const uint32_t on = (bits >> (4 * j + e)) & 1u;
+            if (on) place[k] = (uint16_t)(j * 256 + lane * 4 + e);
+            k += on;
         }
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const uint32_t avail = (uint32_t)(p + n <= cap ? n : cap - p);
+    wave_lds_fence();
     constexpr int U = 4;
     for (uint32_t i0 = lane; i0 < avail; i0 += U * kWave) {
         uint32_t r[U];
@@ -242,9 +314,7 @@ __device__ __forceinline__ void write_unit(uint32_t bits, int64_t base, unsigned
             put((uint32_t *)rowids, x0);
         }
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_lds_fence();
 }
 
 // Writes the qualifying rows of every wave tile at its offset, in row order,
@@ -263,7 +333,7 @@ __global__ __launch_bounds__(kScanBlock) void write_kernel(const uint32_t *tile_
     constexpr int NW = kScanBlock / kWave;
     constexpr int UPT = TILE / kUnitRows;   // units of a tile: 1 or 2
     static_assert(UPT == 1 || UPT == 2, "units of 1,024 rows");
-    __shared__ uint16_t s_place[NW][kUnitRows];
+    __shared__ __attribute__((aligned(16))) uint32_t s_buf[NW][kUnitRows + 4];
     __shared__ uint32_t s_sum[NW];
     const int wave = wave_id(), lane = lane_id();
     uint32_t before = 0;
@@ -316,7 +386,7 @@ __global__ __launch_bounds__(kScanBlock) void write_kernel(const uint32_t *tile_
                 bits &= 0xffffu;
             }
             if (!__any(bits != 0u) || o0 >= cap) continue;
-            write_unit<RPT>(bits, base, o0, pa, rowids, cap, s_place[wave]);
+            write_unit<RPT>(bits, base, o0, pa, rowids, cap, t + 1 < ntiles, s_buf[wave]);
         }
     }
 }
