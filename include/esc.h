@@ -148,7 +148,7 @@ int esc_ctx_num_cus(const esc_ctx *ctx, int *out);
 /* Fraction of a wave tile's rows from which the cost model prices a
  * materialization's projected columns as read whole rather than gathered (1/128
  * unless ESC_DENSE_SHIFT sets another power of two; the write pass itself
- * reads only the sectors that hold qualifying rows at any density). */
+ * reads whole columns from an eighth of 1,024 rows on, whatever this is). */
 int esc_ctx_dense_fraction(const esc_ctx *ctx, double *out);
 
 /* ------------------------------------------------------------------ tables
