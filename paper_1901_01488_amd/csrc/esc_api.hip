@@ -493,20 +493,13 @@ static int materialize_launch(esc_ctx *ctx, const esc_table *t, const esc_pred *
         if (!own) launch_scan(tiles, L.ntiles, offsets, h, total, s);
         // pass 3: write
         if (capacity > 0) {
-            WriteFn fn = write_fn(rpt);
-            // tiles of a block: one unit for each of its waves, up to eight
-            // as long as there are eight blocks for every CU
-            const int64_t least = kScanBlock / 64 * 1024 / (64 * (int64_t)rpt);
-            const int64_t tpb = std::max(least, std::min(8 * least, L.ntiles / (8 * (int64_t)ctx->num_cus) / least * least));
-            const int64_t blocks_needed = (L.ntiles + tpb - 1) / tpb;
-            int64_t grid = blocks_needed;
-            if (!own) {
-                const int occ = occupancy((const void *)fn, kScanBlock, 0);
-                grid = std::min(grid, (int64_t)ctx->num_cus * (ctx->mat_bpc > 0 ? std::min(ctx->mat_bpc, occ) : occ));
-            }
-            hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(kScanBlock), 0, s, bits, tiles,
-                               own ? nullptr : offsets, L.ntiles, (int)tpb, pa, dev_rowids, (unsigned long long)capacity,
-                               h, total);
+            // one unit a wave, in as many blocks as that takes
+            WriteFn fn = write_fn(rpt, own);
+            int64_t grid = (L.ntiles * 64 * rpt / 1024 + kScanBlock / 64 - 1) / (kScanBlock / 64);
+            if (!own && ctx->mat_bpc > 0)
+                grid = std::min(grid, (int64_t)ctx->num_cus * std::min(ctx->mat_bpc, occupancy((const void *)fn, kScanBlock, 0)));
+            hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(kScanBlock), 0, s, bits, tiles, offsets, L.ntiles, pa,
+                               dev_rowids, (unsigned long long)capacity, h, total);
         }
     }
     hipError_t e = hipGetLastError();

@@ -64,14 +64,14 @@ struct WsHeader {
 static_assert(sizeof(WsHeader) == 64, "workspace header is 64 bytes");
 
 typedef void (*CountFn)(const Program, const ColPtrs, int64_t, WsHeader *, unsigned long long *, const TileOut);
-typedef void (*WriteFn)(const uint32_t *, const uint32_t *, const uint32_t *, int64_t, int, const ProjArgs, int32_t *,
+typedef void (*WriteFn)(const uint32_t *, const uint32_t *, const uint32_t *, int64_t, const ProjArgs, int32_t *,
                         unsigned long long, WsHeader *, unsigned long long *);
 // Tiles up to which every block of the write pass finds its own offset (the
-// sum of the counts before it: about 2,000 blocks read half of them each, from
-// their L2) and no scan is launched.  60M rows, 29,297 tiles: 235 us a star
-// selection with the scan, 227 without; the scan's time grows with the tiles,
-// the sums' with tiles times blocks, and they meet at about 50,000.
-constexpr int64_t kOwnPrefixTiles = 40960;
+// sum of the counts before it, read from the L2s) and no scan is launched.
+// The sums grow with tiles times blocks: counts and write passes of 0.05 % of
+// the rows, one column, with the scan and without, 6M rows 21 and 18 us, 12M
+// 28 and 26, 20M (9,766 tiles) 34 and 34, 28M 42 and 44, 40M 53 and 58.
+constexpr int64_t kOwnPrefixTiles = 12288;
 
 CountFn count_fn(int nslots, int rpt, bool udf, bool tiles);
 constexpr int kCompactRPT = 16;   // rows per lane of the single-pass compaction
@@ -81,7 +81,7 @@ typedef void (*CompactFn)(const Program, const ColPtrs, int64_t, unsigned long l
 CompactFn compact_fn(int nslots, bool udf);
 int count_rpt(int variant, int nslots, int ninsn, bool tiles, int64_t nrows, int cus);
 int count_bpc(int variant, int nslots, int bpc, bool tiles);
-WriteFn write_fn(int rpt);
+WriteFn write_fn(int rpt, bool own);
 typedef void (*ConjFn)(const ConjPack, const Program *, int, const ColPtrs, int64_t, unsigned long long *);
 ConjFn conj_fn(int nslots, bool udf, bool packed);
 void launch_zero(unsigned long long *p, int64_t nwords, hipStream_t s);

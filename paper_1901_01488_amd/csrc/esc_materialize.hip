@@ -184,13 +184,11 @@ __device__ __forceinline__ void wave_lds_fence()
 // column's groups, places the values in LDS by rank and writes aligned
 // 16-byte groups (the last tile's units, whose rows may end inside a group,
 // excepted).  Two materializations on 40M rows, one, three and four columns,
-// before / a row a lane throughout / now: 79 % of the rows 320, 544, 659 /
-// 358, 616, 804 / 275, 510, 584 us; 35 %: 235, 423, 513 / 240, 424, 528 /
-// 213, 391, 431.  The line at a quarter of the rows instead of an eighth costs
-// 18 to 22 % of them 3 to 10 % (200, 347, 402 against 195, 340, 366); below it
-// both ways meet.  The 89 registers of both ways together leave five waves a
-// SIMD: eight sparse selections on 6M rows take 316 us, 303 with the 48 of a
-// row a lane alone; held to 80 or 64 registers 316 and 324.
+// staged by chunks / a row a lane throughout / now: 79 % of the rows 320, 544,
+// 659 / 358, 616, 804 / 248, 461, 531 us; 35 %: 235, 423, 513 / 240, 424, 528 /
+// 198, 353, 393.  The line at a quarter of the rows instead of an eighth cost
+// 18 to 22 % of them 3 to 10 % (200, 347, 402 against 195, 340, 366, with runs
+// of units a wave); below it both ways meet.
 constexpr int kUnitRows = 1024;
 constexpr uint32_t kDenseRows = kUnitRows / 8;
 
@@ -318,14 +316,23 @@ __device__ __forceinline__ void write_unit(uint32_t bits, int64_t base, unsigned
 }
 
 // Writes the qualifying rows of every wave tile at its offset, in row order,
-// from the lane masks of the count pass.  A block takes `tpb` tiles at a time
-// (at most 64), its waves their units in turn.  With offsets (scan_kernel's)
-// it walks the table; without them (offsets null: at most kOwnPrefixTiles
-// tiles, one block per tpb tiles) each block sums the counts of the tiles
-// before its own, and the last one stores the total.
-template <int RPT>
-__global__ __launch_bounds__(kScanBlock) void write_kernel(const uint32_t *tile_bits, const uint32_t *counts,
-                                                           const uint32_t *offsets, int64_t ntiles, int tpb,
+// from the lane masks of the count pass: one unit a wave, in as many blocks as
+// that takes, everything that a unit needs before its rows (masks, counts or
+// offsets) read at once.  OWN: the block sums the counts of the tiles before
+// its own and the last one stores the total (kOwnPrefixTiles); else the
+// offsets are scan_kernel's.
+// A wave that goes on to another unit waits for its stores before it sees its
+// next loads (one counter in order), so runs of units a wave cost dense tables
+// most: write passes with their counts on 100M rows, 80 % of them, three
+// columns: 623 us with 16 tiles a block in turn, 1,280 blocks, 553 now, and
+// 604 with every 256-row chunk staged and plain stores; 60M, 80 %, one column:
+// 185, 161 and 202; 60M, 2 %, one column: 92, 83 and 110.  One unit a wave
+// costs sparse ones the launch of the blocks: 100M, 0.01 %, no column: 104,
+// against 101 and 99.
+template <int RPT, bool OWN>
+__global__ __launch_bounds__(kScanBlock) void write_kernel(const uint32_t *__restrict__ tile_bits,
+                                                           const uint32_t *__restrict__ counts,
+                                                           const uint32_t *__restrict__ offsets, int64_t ntiles,
                                                            const ProjArgs pa, int32_t *rowids, unsigned long long cap,
                                                            WsHeader *ws, unsigned long long *total)
 {
@@ -334,59 +341,78 @@ __global__ __launch_bounds__(kScanBlock) void write_kernel(const uint32_t *tile_
     constexpr int UPT = TILE / kUnitRows;   // units of a tile: 1 or 2
     static_assert(UPT == 1 || UPT == 2, "units of 1,024 rows");
     __shared__ __attribute__((aligned(16))) uint32_t s_buf[NW][kUnitRows + 4];
-    __shared__ uint32_t s_sum[NW];
     const int wave = wave_id(), lane = lane_id();
-    uint32_t before = 0;
-    if (!offsets) {
-        const int64_t t0 = (int64_t)blockIdx.x * tpb;
+    const int64_t nunits = ntiles * UPT;
+    // the unit u of the tile's masks `bits`, whose first row goes to o0
+    auto put = [&](int64_t u, uint32_t bits, uint32_t o0) {
+        const int64_t t = u / UPT;
+        int64_t base = t * TILE;
+        if constexpr (UPT == 2) {
+            if (u & 1) {
+                o0 += wave_sum((uint32_t)__popc(bits & 0xffffu));
+                bits >>= 16;
+                base += kUnitRows;
+            }
+            bits &= 0xffffu;
+        }
+        if (!__any(bits != 0u) || o0 >= cap) return;   // wave-uniform
+        write_unit<RPT>(bits, base, o0, pa, rowids, cap, t + 1 < ntiles, s_buf[wave]);
+    };
+    if constexpr (OWN) {
+        constexpr int TPB = NW / UPT;   // tiles of a block
+        __shared__ uint32_t s_sum[NW];
+        const int64_t t0 = (int64_t)blockIdx.x * TPB, u = (int64_t)blockIdx.x * NW + wave;
+        const uint32_t bits = u < nunits ? tile_bits[u / UPT * kWave + lane] : 0u;
+        const uint32_t cnt = lane < TPB && t0 + lane < ntiles ? counts[t0 + lane] : 0u;
         uint32_t sum = 0;
-        for (int64_t i = threadIdx.x * 4; i < t0; i += 4 * kScanBlock) {
-            const u32x4 q = *(const u32x4 *)(counts + i);   // t0 may end inside the four
+        constexpr int NQ = 4;   // loads in flight
+        for (int64_t i0 = threadIdx.x * 4; i0 < t0; i0 += NQ * 4 * kScanBlock) {
+            u32x4 q[NQ];
 #pragma unroll
-            for (int e = 0; e < 4; e++) sum += i + e < t0 ? q[e] : 0u;
+            for (int k = 0; k < NQ; k++) {
+                const int64_t i = i0 + k * 4 * kScanBlock;
+                q[k] = u32x4{0u, 0u, 0u, 0u};
+                if (i < t0) q[k] = *(const u32x4 *)(counts + i);   // t0 may end inside the four
+            }
+#pragma unroll
+            for (int k = 0; k < NQ; k++)
+#pragma unroll
+                for (int e = 0; e < 4; e++) sum += i0 + k * 4 * kScanBlock + e < t0 ? q[k][e] : 0u;
         }
         sum = wave_sum(sum);
         if (lane == 0) s_sum[wave] = sum;
         __syncthreads();
-        for (int w = 0; w < NW; w++) before += s_sum[w];
-    }
-    for (int64_t t0 = (int64_t)blockIdx.x * tpb; t0 < ntiles; t0 += (int64_t)gridDim.x * tpb) {
-        const int nt = (int)(ntiles - t0 < tpb ? ntiles - t0 : tpb);
-        // lane i: the i-th tile's count and offset
-        uint32_t cnt = lane < nt ? counts[t0 + lane] : 0u, off;
-        if (offsets) {
-            off = lane < nt ? offsets[t0 + lane] : 0u;
-        } else {
-            off = cnt;
+        uint32_t off = 0, mine = 0, all = 0;
+        for (int w = 0; w < NW; w++) off += s_sum[w];
 #pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const uint32_t x = __shfl_up(off, o, 64);
-                if (lane >= o) off += x;
-            }
-            off += before - cnt;
-            if (t0 + nt == ntiles && wave == 0 && lane == nt - 1) {
-                ws->result = off + cnt;
-                if (total) *total = off + cnt;
-            }
-        }
-        for (int u = wave; u < nt * UPT; u += NW) {
-            const int i = u / UPT;
+        for (int i = 0; i < TPB; i++) {
             const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)cnt, i);
-            uint32_t o0 = (uint32_t)__builtin_amdgcn_readlane((int)off, i);
-            if (c == 0 || o0 >= cap) continue;   // wave-uniform
-            const int64_t t = t0 + i;
-            uint32_t bits = tile_bits[t * kWave + lane];
-            int64_t base = t * TILE;
-            if constexpr (UPT == 2) {
-                if (u & 1) {
-                    o0 += wave_sum((uint32_t)__popc(bits & 0xffffu));
-                    bits >>= 16;
-                    base += kUnitRows;
-                }
-                bits &= 0xffffu;
-            }
-            if (!__any(bits != 0u) || o0 >= cap) continue;
-            write_unit<RPT>(bits, base, o0, pa, rowids, cap, t + 1 < ntiles, s_buf[wave]);
+            if (i < wave / UPT) off += c;
+            else all += c;
+            if (i == wave / UPT) mine = c;
+        }
+        if (t0 + TPB >= ntiles && threadIdx.x == 0) {   // wave 0: all of the block's tiles lie behind `off`
+            ws->result = off + all;
+            if (total) *total = off + all;
+        }
+        if (mine != 0u && off < cap) put(u, bits, off);
+    } else {
+        // the loop is for grids of fewer blocks (esc_ctx::mat_bpc)
+        uint32_t bits = 0, o0 = 0, o1 = 0;
+        auto load = [&](int64_t u) {
+            if (u >= nunits) return;
+            const int64_t t = u / UPT;
+            bits = tile_bits[t * kWave + lane];
+            o0 = offsets[t];
+            o1 = offsets[t + 1];
+        };
+        int64_t u = (int64_t)blockIdx.x * NW + wave;
+        for (load(u); u < nunits;) {
+            const int64_t next = u + (int64_t)gridDim.x * NW;
+            const uint32_t b = bits, first = o0, last = o1;
+            load(next);
+            if (first != last && first < cap) put(u, b, first);
+            u = next;
         }
     }
 }
@@ -499,9 +525,11 @@ CompactFn compact_fn(int nslots, bool udf)
     return udf ? compact_table_impl<true>(nslots, S{}) : compact_table_impl<false>(nslots, S{});
 }
 
-WriteFn write_fn(int rpt)
+WriteFn write_fn(int rpt, bool own)
 {
-    return rpt == 16 ? write_kernel<16> : write_kernel<32>;   // counts that store tiles run one of the two
+    // counts that store tiles run 16 or 32 rows per lane
+    if (own) return rpt == 16 ? write_kernel<16, true> : write_kernel<32, true>;
+    return rpt == 16 ? write_kernel<16, false> : write_kernel<32, false>;
 }
 
 void launch_zero(unsigned long long *p, int64_t nwords, hipStream_t s)
