@@ -348,11 +348,10 @@ bool plan_index(const esc_batch *b, const esc_batch_opts &o, bool small, std::ve
         index_order(src, order, (int)order.size() > gmax);
         std::vector<char> taken(mem.size(), 0);
         for (size_t i = 0; i < order.size();) {
-            int n = (int)std::min<size_t>(gmax, order.size() - i);
             IndexGroup g;
             const size_t blob0 = plan.blob.size();
-            // fewer predicates need fewer boundaries, columns and layers
-            while (n > 0 && !build_index(src, &order[i], n, T.dtypes.data(), g, plan.blob)) n = n > 32 ? n / 64 * 32 : n / 2;
+            const int n = cut_group(src, &order[i], (int)std::min<size_t>(gmax, order.size() - i), T.dtypes.data(), g,
+                                    plan.blob);
             if (n == 0) {
                 i++;
                 continue;

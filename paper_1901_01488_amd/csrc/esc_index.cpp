@@ -345,4 +345,11 @@ bool build_index(const IndexSource &src, const int *member, int n, const int32_t
     return true;
 }
 
+int cut_group(const IndexSource &src, const int *member, int n, const int32_t *dtypes, IndexGroup &g,
+              std::vector<uint32_t> &blob)
+{
+    while (n > 0 && !build_index(src, member, n, dtypes, g, blob)) n = n > 32 ? std::max(32, n / 64 * 32) : n / 2;
+    return n;
+}
+
 }  // namespace esc

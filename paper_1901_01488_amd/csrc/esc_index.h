@@ -118,4 +118,10 @@ void index_order(const IndexSource &src, std::vector<int> &order, bool by_column
 bool build_index(const IndexSource &src, const int *member, int n, const int32_t *dtypes, IndexGroup &g,
                  std::vector<uint32_t> &blob);
 
+// The index of as many of member[0 .. n) as fit one, from the first on: all
+// of them, else whole 32s, else halves; their number, 0 if none fits (and blob
+// as before).  Fewer predicates need fewer boundaries, columns and layers.
+int cut_group(const IndexSource &src, const int *member, int n, const int32_t *dtypes, IndexGroup &g,
+              std::vector<uint32_t> &blob);
+
 }  // namespace esc
