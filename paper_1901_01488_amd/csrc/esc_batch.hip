@@ -336,6 +336,9 @@ bool plan_index(const esc_batch *b, const esc_batch_opts &o, bool small, std::ve
     struct Planned { size_t table; double cost; };
     std::vector<Planned> planned;
     double total = 0.0;
+    size_t npreds = 0;
+    for (const std::vector<int> &m : members) npreds += m.size();
+    IndexRoom room(std::max(b->cap_counts, npreds), npreds, b->tables.size());
     for (size_t t = 0; t < members.size(); t++) {
         const TableInfo &T = b->tables[t];
         std::vector<int> &mem = members[t];
@@ -359,14 +362,15 @@ bool plan_index(const esc_batch *b, const esc_batch_opts &o, bool small, std::ve
             double by_interp = 0.0;
             for (int j = 0; j < n; j++) by_interp += interp_cost(*b->src[mem[order[i + j]]]);
             const double cost = index_cost(g);
-            if (kIndexGain * cost > by_interp) {
-                if (!small || n < kIndexFewest || fills_chip(b, T.nrows) || kIndexGainSmall * cost > by_interp) {
-                    plan.blob.resize(blob0);
-                    i += n;
-                    continue;
-                }
-                used_small = true;
+            const bool gains = kIndexGain * cost <= by_interp;
+            const bool gains_small =
+                small && n >= kIndexFewest && !fills_chip(b, T.nrows) && kIndexGainSmall * cost <= by_interp;
+            if ((!gains && !gains_small) || !room.take(g, n)) {
+                plan.blob.resize(blob0);
+                i += n;
+                continue;
             }
+            if (!gains) used_small = true;
             IndexGroupRef r{};
             r.words = g.words;
             r.rec = g.rec;
@@ -529,19 +533,16 @@ struct BatchLayout {
     size_t counts, plan, bytes;
 };
 
-// items: work items of the interpreter when it counts every predicate.  An
-// index takes the place of its predicates' programs (at most 77 KB for what
-// would be 128 programs of 2 KB, and groups of fewer are chosen only over
-// programs that take longer); its work items are extra.
+// items: work items of the interpreter when it counts every predicate; those
+// of the indexes are extra.
 BatchLayout batch_layout(const esc_batch *b, size_t pcap, size_t items)
 {
     BatchLayout L;
     L.counts = 0;
     L.plan = up256(pcap * sizeof(unsigned long long));
     L.bytes = L.plan + sizeof(BatchHeader) + up256(pcap * sizeof(int32_t)) + up256(pcap * sizeof(BatchGroup)) +
-              up256(pcap * sizeof(Program)) + up256(items * sizeof(BatchItem)) +
-              up256((7 * (size_t)index_grid(b) + pcap) * sizeof(BatchItem)) +
-              up256((b->tables.size() + pcap / 32 + 1) * sizeof(IndexGroupRef)) + 8 * 256;
+              up256(index_room(pcap, b->tables.size())) + up256(items * sizeof(BatchItem)) +
+              up256((7 * (size_t)index_grid(b) + pcap) * sizeof(BatchItem)) + 8 * 256;
     return L;
 }
 
@@ -637,7 +638,9 @@ int install(esc_batch *b, const esc_batch_opts &o)
     Plan plan;
     int rc = build_plan(b, o, grid, true, true, plan);
     if (rc) return rc;
-    // predicate indexes that do not fit the workspace give way to programs
+    // the indexes have room (IndexRoom); the interpreter's items of predicates
+    // without one can be more than the workspace was sized for: then, as far as
+    // they fit, programs for all
     if (plan_bytes(plan) > b->cap_plan && !plan.igroups.empty() && (rc = build_plan(b, o, grid, false, true, plan))) return rc;
     if (plan_bytes(plan) > b->cap_plan)
         return fail(ESC_ERR_OOM, "the plan takes %zu bytes (%zu work items), the workspace holds %zu", plan_bytes(plan),

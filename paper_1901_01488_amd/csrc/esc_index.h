@@ -118,6 +118,36 @@ void index_order(const IndexSource &src, std::vector<int> &order, bool by_column
 bool build_index(const IndexSource &src, const int *member, int n, const int32_t *dtypes, IndexGroup &g,
                  std::vector<uint32_t> &blob);
 
+// The bytes of a workspace that hold programs and indexes: for each of the
+// predicates it was sized for the sixteenth of a largest index and its group
+// (more than a program takes), and a largest index for every table and one more.  A group
+// that is given room leaves every other predicate its own, so the indexes a
+// plan chooses always fit, whichever predicates an update brings; groups of 16
+// and more always find room.
+constexpr size_t kIndexPredBytes = (kIndexMaxWords * 4 + 512) / 16;
+static_assert(kIndexPredBytes >= sizeof(Program), "a predicate's share holds its program");
+static_assert(sizeof(IndexGroupRef) <= 512, "16 predicates' shares hold a largest index and its group");
+
+inline size_t index_room(size_t npreds, size_t ntables)
+{
+    return npreds * kIndexPredBytes + (ntables + 1) * kIndexMaxWords * 4;
+}
+
+struct IndexRoom {
+    int64_t left;   // beside the shares of the predicates without an index
+    // of a workspace for cap predicates, when npreds are counted
+    IndexRoom(size_t cap, size_t npreds, size_t ntables)
+        : left((int64_t)index_room(cap, ntables) - (int64_t)(npreds * kIndexPredBytes)) {}
+    // room for an index of g over n predicates, if there is; their shares go to it
+    bool take(const IndexGroup &g, int n)
+    {
+        const int64_t after = left + n * (int64_t)kIndexPredBytes - 4 * (int64_t)g.nwords - (int64_t)sizeof(IndexGroupRef);
+        if (after < 0) return false;
+        left = after;
+        return true;
+    }
+};
+
 // The index of as many of member[0 .. n) as fit one, from the first on: all
 // of them, else whole 32s, else halves; their number, 0 if none fits (and blob
 // as before).  Fewer predicates need fewer boundaries, columns and layers.
