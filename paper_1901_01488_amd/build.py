@@ -27,6 +27,7 @@ SOURCES = [
     "esc_types.cpp",
     "esc_api.hip",
     "esc_count.hip",
+    "esc_count_parts.hip",
     "esc_conj.hip",
     "esc_materialize.hip",
     "esc_batch.hip",

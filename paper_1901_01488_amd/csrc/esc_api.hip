@@ -312,14 +312,15 @@ static int count_launch(esc_ctx *ctx, const esc_table *t, const esc_pred *p, voi
         if (!tiles && need_tiles) return fail(ESC_ERR_OOM, "workspace of %zu bytes, %zu needed", ws_bytes, Lt.bytes);
         const int rpt = count_rpt(ctx->count_variant, P.nslots, P.ninsn, tiles, t->nrows, ctx->num_cus);
         const WsLayout L = ws_layout(t->nrows, rpt);
-        TileOut to{nullptr, nullptr, 0ull, 0ull, 0};
+        TileOut to{nullptr, nullptr, 0ull, 0ull};
         if (tiles) {
             to.counts = (uint32_t *)((char *)dev_ws + L.counts_off);
             to.bits = (uint32_t *)((char *)dev_ws + L.bits_off);
             to.expect = expect;
             to.stamp = expect ? expect : new_stamp();
         }
-        CountFn fn = count_fn(P.nslots, rpt, (P.flags & P_HAS_UDF) != 0, tiles);
+        const bool udf = (P.flags & P_HAS_UDF) != 0;
+        CountFn fn = count_fn(P.nslots, rpt, udf, tiles);
         const int occ = occupancy((const void *)fn, kScanBlock, 0);
         int64_t grid = (int64_t)ctx->num_cus *
                        (ctx->bpc > 0 ? count_bpc(ctx->count_variant, P.nslots, ctx->bpc, tiles) : occ);
@@ -331,7 +332,7 @@ static int count_launch(esc_ctx *ctx, const esc_table *t, const esc_pred *p, voi
         // a blocking count whose blocks each take one round gets a word of
         // each; on longer ones the atomics of the blocks' ends spread out
         if (host_words && !tiles && grid == blocks_needed && grid <= kCountParts) {
-            to.parts = 1;
+            fn = count_parts_fn(P.nslots, rpt, udf);
             *host_words = (int)grid;
         }
         hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(kScanBlock), to.counts ? kTileBufBytes : 0, s, P,

@@ -47,7 +47,6 @@ struct TileOut {
     uint32_t *bits;
     unsigned long long stamp;
     unsigned long long expect;
-    int32_t parts;   // plain counts: out holds one host word per block
 };
 
 // The count's running word: rows in bits 0..kTotalBits-1, blocks done above
@@ -74,6 +73,8 @@ typedef void (*WriteFn)(const uint32_t *, const uint32_t *, const uint32_t *, in
 constexpr int64_t kOwnPrefixTiles = 12288;
 
 CountFn count_fn(int nslots, int rpt, bool udf, bool tiles);
+// a plain count whose out holds one host word per block
+CountFn count_parts_fn(int nslots, int rpt, bool udf);
 constexpr int kCompactRPT = 16;   // rows per lane of the single-pass compaction
 typedef void (*CompactFn)(const Program, const ColPtrs, int64_t, unsigned long long *, unsigned int *,
                           const ProjArgs, const ProjSlots, int32_t *, unsigned long long, uint32_t,
