@@ -59,7 +59,8 @@ struct TableHeader {
     uint32_t dup;        // some key has several rows
     uint32_t nokey;      // rows whose key is kNoKey (hash form)
     uint32_t rows;       // build rows
-    uint32_t pad[10];
+    uint32_t parts;      // ranges of 2^kPartBits values that build_parts_kernel takes, 0: build_kernel inserts the keys
+    uint32_t pad[9];
     int32_t part[kMinMaxParts][2];
 };
 static_assert(sizeof(TableHeader) == 256, "the slots follow at byte 256");
@@ -147,13 +148,36 @@ __device__ __forceinline__ void fill_words(uint32_t *p, int64_t n4, uint32_t v)
         ((u32x4 *)p)[i] = q;
 }
 
+// Bitmaps of many keys are built in LDS, 2^20 bits by block: a random atomic
+// on memory costs as much as one on a whole 64-byte line (26 * 10^9 lines a
+// second measured), so the blocks of a part of the range scan slices of the
+// keys and then OR their 128 KiB into memory line by line.  3M keys of a range
+// of 20M: 63 us, against 116 us by one atomic per key.  The estimate: n / 26000 us against
+// the scan of the keys by every part (0.12 cycles a key) and 30 us to write.
+constexpr int kPartBits = 20;
+constexpr int kPartBytes = 1 << (kPartBits - 3);
+constexpr int kPartBlock = 1024;
+constexpr int64_t kPartKeys = 1 << 20;   // keys from which this kernel is launched at all
+
+// Parts of a table built so by `blocks` blocks, 0 if it is not: asked once, by
+// the kernel that writes the header, so that exactly one of the two build
+// kernels inserts the keys.
+__device__ __forceinline__ uint32_t build_parts(uint32_t mode, uint32_t span, int64_t n, int blocks)
+{
+    const int64_t parts = (int64_t)(span >> kPartBits) + 1;
+    const bool pays = n >= kPartKeys && mode == TAB_BITMAP && parts <= blocks &&
+                      (float)n * (1.0f / 26000.0f) > 30.0f + (float)n * (float)parts / (float)blocks * (0.12f / 2100.0f);
+    return pays ? (uint32_t)parts : 0u;
+}
+
 // Chooses the form from the keys' range (every block alike), clears what that
 // form uses, and writes the header.  nparts: minima and maxima in the header,
-// 0 for a range that every block finds itself (kMinMaxNone keys at most).
+// 0 for a range that every block finds itself (kMinMaxNone keys at most);
+// part_blocks: blocks of build_parts_kernel.
 constexpr int kFillBlock = 256;
 
 __global__ __launch_bounds__(kFillBlock) void fill_table_kernel(const int32_t *__restrict__ keys, TableHeader *h,
-                                                                int64_t n, int64_t slots, int nparts)
+                                                                int64_t n, int64_t slots, int nparts, int part_blocks)
 {
     int32_t lo = INT_MAX, hi = INT_MIN;
     if (nparts == 0) {
@@ -186,6 +210,7 @@ __global__ __launch_bounds__(kFillBlock) void fill_table_kernel(const int32_t *_
         h->dup = mode == TAB_COUNTS;
         h->nokey = 0u;
         h->rows = (uint32_t)n;
+        h->parts = build_parts(mode, span, n, part_blocks);
     }
 }
 
@@ -206,32 +231,14 @@ __device__ __forceinline__ void add_further_row(uint32_t *a, uint32_t slots, int
     }
 }
 
-// Bitmaps of many keys are built in LDS, 2^20 bits by block: a random atomic
-// on memory costs as much as one on a whole 64-byte line (26 * 10^9 lines a
-// second measured), so the blocks of a part of the range scan slices of the
-// keys and then OR their 128 KiB into memory line by line.  3M keys of a range
-// of 20M: 63 us, against 116 us by one atomic per key.  The estimate: n / 26000 us against
-// the scan of the keys by every part (0.12 cycles a key) and 30 us to write.
-constexpr int kPartBits = 20;
-constexpr int kPartBytes = 1 << (kPartBits - 3);
-constexpr int kPartBlock = 1024;
-constexpr int64_t kPartKeys = 1 << 20;   // keys from which this kernel is launched at all
-
-__device__ __forceinline__ bool built_in_parts(uint32_t mode, uint32_t span, int64_t n, int blocks)
-{
-    const int64_t parts = (int64_t)(span >> kPartBits) + 1;
-    return n >= kPartKeys && mode == TAB_BITMAP && parts <= blocks &&
-           (float)n * (1.0f / 26000.0f) > 30.0f + (float)n * (float)parts / (float)blocks * (0.12f / 2100.0f);
-}
-
 __global__ __launch_bounds__(kPartBlock) void build_parts_kernel(const int32_t *__restrict__ keys, int64_t n,
                                                                  TableHeader *h, uint32_t slots, int shift)
 {
     extern __shared__ uint32_t s_part[];
     const int32_t kmin = h->kmin;
     const uint32_t span = h->span;
-    if (!built_in_parts(h->mode, span, n, (int)gridDim.x)) return;
-    const int parts = (int)(span >> kPartBits) + 1;
+    const int parts = (int)h->parts;
+    if (parts == 0) return;
     const int slices = (int)gridDim.x / parts;
     const uint32_t part = blockIdx.x % (unsigned)parts;
     const int slice = (int)(blockIdx.x / (unsigned)parts);
@@ -278,12 +285,12 @@ __global__ __launch_bounds__(kPartBlock) void build_parts_kernel(const int32_t *
 // are in it, so every search ends: at least half of the key slots stay empty (a key
 // takes one slot, or two for its two or more rows).
 __global__ __launch_bounds__(256) void build_kernel(const int32_t *__restrict__ keys, int64_t n, TableHeader *h,
-                                                    uint32_t slots, int shift, int part_blocks)
+                                                    uint32_t slots, int shift)
 {
     uint32_t *a = area(h);
     const uint32_t mode = h->mode;
     const int32_t kmin = h->kmin;
-    if (built_in_parts(mode, h->span, n, part_blocks)) return;
+    if (h->parts != 0u) return;
     bool dup = false;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const uint32_t key = (uint32_t)keys[i];
@@ -682,10 +689,10 @@ int esc_hash_build(esc_ctx *ctx, const int32_t *dev_keys, int64_t nkeys, void *d
     }
     const int64_t fill_blocks = std::min<int64_t>((slots / 2 + kFillBlock - 1) / kFillBlock, grid);   // 16 bytes per thread
     hipLaunchKernelGGL(fill_table_kernel, dim3((unsigned)fill_blocks), dim3(kFillBlock), 0, s, dev_keys, h, nkeys, slots,
-                       nparts);
+                       nparts, ctx->num_cus);
     if (nkeys > 0) {
         const int shift = 32 - log2_exact(slots);
-        // one of the two kernels does the work, by the range that the device found
+        // one of the two kernels does the work, as the header says
         if (nkeys >= kPartKeys) {
             hipError_t e = hipFuncSetAttribute((const void *)build_parts_kernel,
                                                hipFuncAttributeMaxDynamicSharedMemorySize, kPartBytes);
@@ -694,7 +701,7 @@ int esc_hash_build(esc_ctx *ctx, const int32_t *dev_keys, int64_t nkeys, void *d
                                h, (uint32_t)slots, shift);
         }
         hipLaunchKernelGGL(build_kernel, dim3((unsigned)std::min<int64_t>((nkeys + 255) / 256, grid)), dim3(256), 0, s,
-                           dev_keys, nkeys, h, (uint32_t)slots, shift, ctx->num_cus);
+                           dev_keys, nkeys, h, (uint32_t)slots, shift);
     }
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? ESC_OK : hip_fail(e, "hash build launch");
