@@ -572,7 +572,8 @@ int esc_decimal64_words(const int64_t *values, int64_t n, int32_t *high, int32_t
  * tables on the others, whose pushed-down selections (Section 2.1) leave
  * them as temporary tables.  A hash table lives in caller-owned device
  * memory of esc_hash_table_bytes(nkeys) bytes (a power of two of 8-byte
- * slots, at least two per key and at least 64, and a header); several rows may
+ * slots, at least two per key and at least 64, and a header), at any multiple
+ * of 8 bytes; several rows may
  * share a key.  What the bytes hold is the library's own (a bitmap, row counts
  * or hashed keys, by the keys' range); they may be copied, but a table is read
  * only by esc_join_count. */

@@ -73,6 +73,9 @@ struct HashRef {
 // Fibonacci hashing: the top bits of key * 2^32 / golden ratio
 __device__ __forceinline__ uint32_t hash_of(uint32_t key) { return key * 0x9E3779B1u; }
 
+// 16 bytes of a table, which may begin at any multiple of 8
+typedef uint32_t slot4 __attribute__((ext_vector_type(4), aligned(8)));
+
 __device__ __forceinline__ uint32_t *area(const TableHeader *h) { return (uint32_t *)((char *)h + sizeof(TableHeader)); }
 
 // ------------------------------------------------------------------ build
@@ -143,9 +146,9 @@ __global__ __launch_bounds__(kMinMaxBlock) void minmax_kernel(const int32_t *__r
 
 __device__ __forceinline__ void fill_words(uint32_t *p, int64_t n4, uint32_t v)
 {
-    const u32x4 q = {v, v, v, v};
+    const slot4 q = {v, v, v, v};
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n4; i += (int64_t)gridDim.x * blockDim.x)
-        ((u32x4 *)p)[i] = q;
+        ((slot4 *)p)[i] = q;
 }
 
 // Bitmaps of many keys are built in LDS, 2^20 bits by block: a random atomic
@@ -310,7 +313,7 @@ __global__ __launch_bounds__(256) void build_kernel(const int32_t *__restrict__ 
             for (uint32_t step = 0; !done && step < slots / 4; step++) {
                 // a slot read as empty may have been taken since: the
                 // exchange below says by whom
-                const u32x4 q = *(const u32x4 *)(a + 4 * (int64_t)b);
+                const slot4 q = *(const slot4 *)(a + 4 * (int64_t)b);
 #pragma unroll
                 for (int e = 0; e < 4; e++) {
                     if (done) continue;
@@ -430,7 +433,7 @@ __device__ __forceinline__ uint32_t lookup(const Side &t, const uint32_t *key, u
 #pragma unroll
     for (int r = 0; r < N; r++) {
         b[r] = ((live >> r) & 1u) ? hash_of(key[r]) >> (t.shift + 2) : 0u;
-        q[r] = *(const u32x4 *)(t.a + 4 * (int64_t)b[r]);
+        q[r] = *(const slot4 *)(t.a + 4 * (int64_t)b[r]);
         if (key[r] == kNoKey && ((live >> r) & 1u)) {
             open &= ~(1u << r);
             hit |= (t.nokey != 0u ? 1u : 0u) << r;
@@ -471,7 +474,7 @@ __device__ __forceinline__ uint32_t lookup(const Side &t, const uint32_t *key, u
         for (int r = 0; r < N; r++) {
             if (!((open >> r) & 1u)) continue;
             b[r] = (b[r] + 1u) & (nb - 1u);
-            q[r] = *(const u32x4 *)(t.a + 4 * (int64_t)b[r]);
+            q[r] = *(const slot4 *)(t.a + 4 * (int64_t)b[r]);
         }
     }
     return hit;
