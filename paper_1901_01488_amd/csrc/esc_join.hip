@@ -155,8 +155,12 @@ __device__ __forceinline__ void fill_words(uint32_t *p, int64_t n4, uint32_t v)
 // on memory costs as much as one on a whole 64-byte line (26 * 10^9 lines a
 // second measured), so the blocks of a part of the range scan slices of the
 // keys and then OR their 128 KiB into memory line by line.  3M keys of a range
-// of 20M: 63 us, against 116 us by one atomic per key.  The estimate: n / 26000 us against
-// the scan of the keys by every part (0.12 cycles a key) and 30 us to write.
+// of 24 parts: a build of 97 us, against 141 by one atomic per key.  The
+// estimate: n / 25000 us for the atomics, against 30 us to write and 150 us for
+// each million keys of a slice.  Both ways in us, by parts and slices a part:
+// 10M keys 40 (6) 301 and 424, 64 (4) 383 and 423, 96 (2) 640 and 427; 50M 48
+// (5) 1,780 and 1,994, 64 (4) 2,068 and 2,012, 96 (2) 3,702 and 2,013; 2M 32 (8)
+// 86 and 102, 64 (4) 112 and 102.
 constexpr int kPartBits = 20;
 constexpr int kPartBytes = 1 << (kPartBits - 3);
 constexpr int kPartBlock = 1024;
@@ -168,8 +172,8 @@ constexpr int64_t kPartKeys = 1 << 20;   // keys from which this kernel is launc
 __device__ __forceinline__ uint32_t build_parts(uint32_t mode, uint32_t span, int64_t n, int blocks)
 {
     const int64_t parts = (int64_t)(span >> kPartBits) + 1;
-    const bool pays = n >= kPartKeys && mode == TAB_BITMAP && parts <= blocks &&
-                      (float)n * (1.0f / 26000.0f) > 30.0f + (float)n * (float)parts / (float)blocks * (0.12f / 2100.0f);
+    if (n < kPartKeys || mode != TAB_BITMAP || parts > blocks) return 0u;
+    const bool pays = (float)n * (1.0f / 25000.0f) > 30.0f + (float)(n / (blocks / parts)) * 150e-6f;
     return pays ? (uint32_t)parts : 0u;
 }
 

@@ -13,7 +13,7 @@ PARTS_WORD = 6   # of the header
 
 def _pays(n, span, cus):
     parts = (span >> 20) + 1
-    return n >= 1 << 20 and parts <= cus and n / 26000.0 > 30.0 + n * parts / cus * (0.12 / 2100.0)
+    return n >= 1 << 20 and parts <= cus and n / 25000.0 > 30.0 + n // (cus // parts) * 150e-6
 
 
 @pytest.mark.parametrize("n,span", [(1_048_575, 1 << 21), (1_048_576, 1 << 21), (1_048_576, (1 << 24) - 1),
