@@ -568,7 +568,8 @@ int esc_count_conjuncts(esc_ctx *ctx, const esc_table *t, const esc_pred *p, voi
         // kernel (10,000 rows 28 us a call with it, the counters' clearing
         // and their copy back, 22 without)
         ConjPack pack;
-        const bool packed = pack_conjuncts(progs, pack);
+        const ConjLoad load = conj_load(progs, nslots);
+        const bool packed = !load.upload && pack_conjuncts(progs, pack);
         const Program *d_progs = (const Program *)dev_ws;
         if (!packed && (e = hipMemcpyAsync(dev_ws, progs.data(), m * sizeof(Program), hipMemcpyHostToDevice, s)) != hipSuccess)
             return hip_fail(e, "upload conjunct programs");
@@ -579,9 +580,15 @@ int esc_count_conjuncts(esc_ctx *ctx, const esc_table *t, const esc_pred *p, voi
         for (int c = 0; c < nslots; c++) cp.p[c] = (const uint32_t *)t->cols[slot_col[c]];
         ConjFn fn = conj_fn(nslots, udf, packed);
         const int lds = m * kScanBlock * (int)sizeof(unsigned long long);
-        // two blocks a CU: 40M star rows take 313 us for four predicates, 334
-        // with one and 321 to 330 with four to eight (10M: 144, 152, 146 to 153)
-        grid = std::min(2 * (int64_t)ctx->num_cus, (int64_t)(kSlotWord / m));
+        grid = 2 * (int64_t)ctx->num_cus;
+        if (load.heavy) {
+            grid = (int64_t)ctx->num_cus *
+                   std::min(occupancy((const void *)fn, kScanBlock, 0), kLdsBytes / (lds + kConjStaticLds));
+            // twice as many where a wave still has four tiles: the ends spread
+            // (40M rows, three IN-lists 297 us, 320 in one round; 10M 80 both)
+            if (2 * grid <= kSlotWord / m && t->nrows >= 2 * grid * 4 * 16 * kScanBlock) grid *= 2;
+        }
+        grid = std::min(grid, (int64_t)(kSlotWord / m));
         const int64_t blocks_needed = (t->nrows + 16 * kScanBlock - 1) / (16 * kScanBlock);
         if (grid > blocks_needed) grid = blocks_needed;
         hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(kScanBlock), lds, s, pack, d_progs, m, cp, t->nrows,

@@ -839,6 +839,18 @@ int split_conjuncts(const esc_pred *p, std::vector<Program> &out, int &nslots, i
     return ESC_OK;
 }
 
+ConjLoad conj_load(const std::vector<Program> &progs, int nslots)
+{
+    int work = 0;
+    for (const Program &P : progs) {
+        work += P.ninsn + 8 * P.ntables;
+        for (int i = 0; i < P.ninsn; i++)
+            if (P.insn[i].op == T_IN_I32 || P.insn[i].op == T_IN_F32) work += P.insn[i].b;
+    }
+    const bool heavy = work > 5 * nslots;
+    return {heavy, heavy && nslots > 6};
+}
+
 static_assert(kMaxConjParts == ESC_MAX_CONJ, "one part per conjunct");
 
 bool pack_conjuncts(const std::vector<Program> &progs, ConjPack &pack)

@@ -19,8 +19,11 @@ namespace esc {
 // before the last tile.  Each block stores its words of that form in pinned
 // host memory, out[block * nconj + conjunct], and the host adds them up: no
 // counters to clear before the scan and no copy after it.
-// Four star predicates on 10M rows 198 -> 144 us, on 40M 354 -> 313; the
-// interpreter's vector work and the wait for the call bound it by then.
+// What bounds it: the columns' bytes for programs of little work (four star
+// predicates, ten column reads in all, 40M rows 313 us = 5.1 TB/s; 354 before),
+// the interpreter's vector instructions for others (conj_load), and below
+// about 3M rows the call (10,000 rows 22 us; 10M star rows 198 -> 144 us for
+// four, 36 us a call for 16 us of their bytes).
 // PACKED: the programs come as one list in the kernel's arguments with their
 // tables in registers; else from memory.
 template <int K, int RPT, bool UDF, bool PACKED>

@@ -48,5 +48,20 @@ int split_conjuncts(const esc_pred *p, std::vector<Program> &out, int &nslots, i
 // The programs as one list with one pool; false if they need more
 // instructions, pool words or slot tables than it holds.
 bool pack_conjuncts(const std::vector<Program> &progs, ConjPack &pack);
+// How split conjuncts on nslots columns run.  Programs of little work for each
+// column they load are bound by the loads and run two blocks a CU: four star
+// predicates on 40M rows take 313 us so, 321 to 332 with four to eight.
+// heavy: others are bound by their own instructions and run all the blocks
+// that registers and LDS hold (an instruction counts one, each constant of a
+// compare list one, a slot table eight).  40M rows, two blocks and all: two
+// IN-lists of 40 on two columns 236 and 189 us, 12 ORs of three on three 288
+// and 218, three udfs on two 161 and 124; two ORs of three 101 and 106.
+// upload: on seven and eight columns heavy programs are read from memory: as an
+// argument, with their tables in registers, they lose a wave (eight columns,
+// six IN-lists, 60M rows 844 against 702 us).
+struct ConjLoad {
+    bool heavy, upload;
+};
+ConjLoad conj_load(const std::vector<Program> &progs, int nslots);
 
 }  // namespace esc

@@ -85,6 +85,8 @@ int count_bpc(int variant, int nslots, int bpc, bool tiles);
 WriteFn write_fn(int rpt, bool own);
 typedef void (*ConjFn)(const ConjPack, const Program *, int, const ColPtrs, int64_t, unsigned long long *);
 ConjFn conj_fn(int nslots, bool udf, bool packed);
+constexpr int kLdsBytes = 160 * 1024;   // of a CU
+constexpr int kConjStaticLds = kScanBlock / 64 * kMaxConj * 8;   // of conj_kernel, beside its counts
 void launch_zero(unsigned long long *p, int64_t nwords, hipStream_t s);
 // offsets of m tile counts in row order; the total goes to ws->result and,
 // when total is not null, to *total
