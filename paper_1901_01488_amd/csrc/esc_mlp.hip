@@ -892,10 +892,14 @@ int esc_mlp_predict(esc_mlp *m, const float *dev_x, int64_t n, float *dev_yhat, 
     if (n < 0 || (n > 0 && (!dev_x || !dev_yhat))) return fail(ESC_ERR_INVALID, "bad arguments");
     if (n == 0) return ESC_OK;
     hipStream_t s = (hipStream_t)stream;
-    // 64 rows a block read each weight half as often, but fill the chip from
-    // twice as many rows on (16,384 rows: 9.6 us by 32, 9.4 by 64; 4,096: 6.2
-    // and 9.3; 262,144: 115 and 107)
-    if (n <= 64ll * m->num_cus)
+    // 64 rows a block read each weight half as often, but every 64 rows a CU
+    // begun take the time of all: 32 rows are faster for up to three such
+    // blocks a CU and for a fifth (us by 32 and by 64: 4,096 rows 6.6 and 9.4,
+    // 16,384 9.6 and 9.6, 18,000 12.0 and 14.0, 24,576 12.6 and 14.2, 28,000
+    // 15.5 and 14.3, 36,000 18.9 and 20.6, 49,152 23.2 and 21.0, 262,144 115
+    // and 107)
+    const int64_t tiles = (n + 32ll * m->num_cus - 1) / (32ll * m->num_cus);
+    if (tiles <= 3 || tiles == 5)
         hipLaunchKernelGGL(forward_kernel<1>, dim3((unsigned)((n + 31) / 32)), dim3(kBlock), 0, s, dev_x, n, m->st.p,
                            m->st.pk, dev_yhat);
     else
