@@ -171,10 +171,11 @@ constexpr int64_t kPartKeys = 1 << 20;   // keys from which this kernel is launc
 // kernels inserts the keys.
 __device__ __forceinline__ uint32_t build_parts(uint32_t mode, uint32_t span, int64_t n, int blocks)
 {
-    const int64_t parts = (int64_t)(span >> kPartBits) + 1;
-    if (n < kPartKeys || mode != TAB_BITMAP || parts > blocks) return 0u;
-    const bool pays = (float)n * (1.0f / 25000.0f) > 30.0f + (float)(n / (blocks / parts)) * 150e-6f;
-    return pays ? (uint32_t)parts : 0u;
+    const uint32_t parts = (span >> kPartBits) + 1u, keys = (uint32_t)n;   // at most 2^30
+    if (n < kPartKeys || mode != TAB_BITMAP || parts > (uint32_t)blocks) return 0u;
+    const bool pays =
+        (float)keys * (1.0f / 25000.0f) > 30.0f + (float)(keys / ((uint32_t)blocks / parts)) * 150e-6f;
+    return pays ? parts : 0u;
 }
 
 // Chooses the form from the keys' range (every block alike), clears what that
