@@ -29,8 +29,10 @@
 
 #include <algorithm>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <new>
+#include <numeric>
 #include <string>
 #include <vector>
 
@@ -168,7 +170,8 @@ __global__ __launch_bounds__(kScanBlock) void batch_kernel(BatchHeader *h, const
                 }
             }
             break;
-        }        __syncthreads();
+        }
+        __syncthreads();
         for (int i = threadIdx.x; i < g.npred; i += kScanBlock) {
             unsigned long long s = 0;
 #pragma unroll
@@ -332,35 +335,35 @@ int index_grid(const esc_batch *b) { return std::max(1, b->ctx->num_cus * kIndex
 
 // Takes the predicates of each table's members that a predicate index counts
 // more cheaply than the interpreter out of members and into the plan.
-// small: whether the rule for small tables may be used; true if it was.
-bool plan_index(const esc_batch *b, const esc_batch_opts &o, bool small, std::vector<std::vector<int>> &members,
-                Plan &plan)
+void plan_index(const esc_batch *b, const esc_batch_opts &o, std::vector<std::vector<int>> &members, Plan &plan)
 {
-    bool used_small = false;
     const int gmax = o.group > 0 ? std::min((int)o.group, kIndexMaxPreds) : kIndexMaxPreds;
-    struct Planned { size_t table; double cost; };
+    struct Planned { size_t table; double cost; bool gains; };   // gains: not only by the rule for small tables
     std::vector<Planned> planned;
-    double total = 0.0;
+    std::vector<std::vector<char>> taken(members.size());
+    bool used_small = false, left = false;   // left: some predicate has no index
     size_t npreds = 0;
     for (const std::vector<int> &m : members) npreds += m.size();
     IndexRoom room(std::max(b->cap_counts, npreds), npreds, b->tables.size());
     for (size_t t = 0; t < members.size(); t++) {
         const TableInfo &T = b->tables[t];
-        std::vector<int> &mem = members[t];
+        const std::vector<int> &mem = members[t];
         IndexSource src;
         plan.blob.reserve(plan.blob.size() + mem.size() * 96);   // about what 128 predicates take
         for (int p : mem) src.add(*b->src[p], T.dtypes.data());
-        std::vector<int> order, at;   // positions in mem
+        std::vector<int> order;   // positions in mem
         for (int i = 0; i < (int)mem.size(); i++)
             if (src.preds[i].nor >= 0) order.push_back(i);
+        left = left || order.size() < mem.size();
         index_order(src, order, (int)order.size() > gmax);
-        std::vector<char> taken(mem.size(), 0);
+        taken[t].assign(mem.size(), 0);
         for (size_t i = 0; i < order.size();) {
             IndexGroup g;
             const size_t blob0 = plan.blob.size();
             const int n = cut_group(src, &order[i], (int)std::min<size_t>(gmax, order.size() - i), T.dtypes.data(), g,
                                     plan.blob);
             if (n == 0) {
+                left = true;
                 i++;
                 continue;
             }
@@ -369,13 +372,14 @@ bool plan_index(const esc_batch *b, const esc_batch_opts &o, bool small, std::ve
             const double cost = index_cost(g);
             const bool gains = kIndexGain * cost <= by_interp;
             const bool gains_small =
-                small && n >= kIndexFewest && !fills_chip(b, T.nrows) && kIndexGainSmall * cost <= by_interp;
+                !left && n >= kIndexFewest && !fills_chip(b, T.nrows) && kIndexGainSmall * cost <= by_interp;
             if ((!gains && !gains_small) || !room.take(g, n)) {
                 plan.blob.resize(blob0);
+                left = true;
                 i += n;
                 continue;
             }
-            if (!gains) used_small = true;
+            used_small = used_small || !gains;
             IndexGroupRef r{};
             r.words = g.words;
             r.rec = g.rec;
@@ -390,18 +394,47 @@ bool plan_index(const esc_batch *b, const esc_batch_opts &o, bool small, std::ve
                 r.cols[k] = IndexColumnRef{(const uint32_t *)T.cols[g.cols[k].col], 4u * (uint32_t)g.cols[k].key_off,
                                            4u * (uint32_t)g.cols[k].rec_off, g.cols[k].levels, g.cols[k].is_float};
             plan.igroups.push_back(r);
-            planned.push_back({t, cost});
-            total += cost * (double)T.nrows;
+            planned.push_back({t, cost, gains});
             for (int j = 0; j < n; j++) {
                 plan.pred_ids.push_back(mem[order[i + j]]);
-                taken[order[i + j]] = 1;
+                taken[t][order[i + j]] = 1;
             }
             i += n;
         }
-        for (int i = 0; i < (int)mem.size(); i++)
-            if (!taken[i]) at.push_back(mem[i]);
-        mem.swap(at);
     }
+    if (used_small && left) {   // the rule for small tables does not hold after all
+        Plan kept;
+        std::vector<Planned> kept_planned;
+        for (size_t gi = 0; gi < planned.size(); gi++) {
+            IndexGroupRef r = plan.igroups[gi];
+            const int32_t *ids = &plan.pred_ids[r.pbegin];
+            if (!planned[gi].gains) {
+                const std::vector<int> &mem = members[planned[gi].table];
+                for (int j = 0; j < r.npred; j++)
+                    taken[planned[gi].table][std::lower_bound(mem.begin(), mem.end(), ids[j]) - mem.begin()] = 0;
+                continue;
+            }
+            const uint32_t *words = &plan.blob[r.blob];
+            r.blob = (uint32_t)kept.blob.size();
+            r.pbegin = (int)kept.pred_ids.size();
+            kept.blob.insert(kept.blob.end(), words, words + r.nwords);
+            kept.pred_ids.insert(kept.pred_ids.end(), ids, ids + r.npred);
+            kept.igroups.push_back(r);
+            kept_planned.push_back(planned[gi]);
+        }
+        plan.blob.swap(kept.blob);
+        plan.pred_ids.swap(kept.pred_ids);
+        plan.igroups.swap(kept.igroups);
+        planned.swap(kept_planned);
+    }
+    for (size_t t = 0; t < members.size(); t++) {
+        std::vector<int> rest;
+        for (size_t i = 0; i < members[t].size(); i++)
+            if (!taken[t][i]) rest.push_back(members[t][i]);
+        members[t].swap(rest);
+    }
+    double total = 0.0;
+    for (const Planned &q : planned) total += q.cost * (double)b->tables[q.table].nrows;
     // About six items of equal cost per block of the persistent grid, each of
     // at least four wave tiles per wave (an item ends with a sum over lanes);
     // with less work than that, one item per block.
@@ -421,7 +454,6 @@ bool plan_index(const esc_batch *b, const esc_batch_opts &o, bool small, std::ve
     }
     std::stable_sort(items.begin(), items.end(), [](const Cost &a, const Cost &c) { return a.cost > c.cost; });
     for (auto &c : items) plan.iitems.push_back(c.it);
-    return used_small;
 }
 
 // use_index: whether predicate indexes may take predicates from the
@@ -434,21 +466,14 @@ int build_plan(const esc_batch *b, const esc_batch_opts &o, int grid, bool use_i
     std::vector<std::vector<int>> members(b->tables.size());
     for (size_t p = 0; p < b->pred_table.size(); p++)
         if (b->constant[p] == 0) members[b->pred_table[p]].push_back((int)p);
-    if (use_index) {
-        const std::vector<std::vector<int>> all = members;
-        if (plan_index(b, o, true, members, plan) &&
-            std::any_of(members.begin(), members.end(), [](const std::vector<int> &m) { return !m.empty(); })) {
-            plan = Plan{};
-            members = all;
-            plan_index(b, o, false, members, plan);
-        }
-    }
+    if (use_index) plan_index(b, o, members, plan);
     // the interpreter's predicate ids come first in its own numbering
     const std::vector<int32_t> index_ids = std::move(plan.pred_ids);
     plan.pred_ids.clear();
     std::vector<int64_t> npreds;
     for (auto &m : members) npreds.push_back((int64_t)m.size());
     const int64_t chunk = chunk_rows_for(b, o, gmax, grid, npreds, !plan.igroups.empty());
+    if (lists) plan.progs.reserve((size_t)std::accumulate(npreds.begin(), npreds.end(), (int64_t)0));
     struct Cost { int64_t cost; BatchItem it; };
     std::vector<Cost> items;
     for (size_t t = 0; t < b->tables.size(); t++) {
@@ -510,18 +535,19 @@ size_t plan_bytes(const Plan &p)
            list_bytes(p.progs) + list_bytes(p.igroups) + list_bytes(p.iitems) + list_bytes(p.blob);
 }
 
-// The plan as the kernels read it.
-void pack_plan(const Plan &p, std::vector<char> &out)
+// The plan as the kernels read it, in plan_bytes(p) bytes.
+void pack_plan(const Plan &p, char *out)
 {
-    out.assign(plan_bytes(p), 0);
     BatchHeader h{};
     h.nitems[0] = (unsigned int)p.items.size();
     h.nitems[1] = (unsigned int)p.iitems.size();
     size_t at = sizeof(BatchHeader);
     auto put = [&](const auto &v, unsigned int &off) {
         off = (unsigned int)at;
-        if (!v.empty()) memcpy(out.data() + at, v.data(), v.size() * sizeof v[0]);
-        at += list_bytes(v);
+        const size_t n = v.size() * sizeof v[0], bytes = list_bytes(v);
+        if (n) memcpy(out + at, v.data(), n);
+        memset(out + at + n, 0, bytes - n);
+        at += bytes;
     };
     put(p.pred_ids, h.ids);
     put(p.groups, h.groups);
@@ -530,7 +556,7 @@ void pack_plan(const Plan &p, std::vector<char> &out)
     put(p.igroups, h.igroups);
     put(p.iitems, h.iitems);
     put(p.blob, h.blob);
-    memcpy(out.data(), &h, sizeof h);
+    memcpy(out, &h, sizeof h);
 }
 
 // Regions of a batch workspace for pcap predicates: counters, then the plan.
@@ -651,9 +677,9 @@ int install(esc_batch *b, const esc_batch_opts &o)
         return fail(ESC_ERR_OOM, "the plan takes %zu bytes (%zu work items), the workspace holds %zu", plan_bytes(plan),
                     plan.items.size() + plan.iitems.size(), b->cap_plan);
     hipStream_t s = b->cap_stream;
-    std::vector<char> packed;
-    pack_plan(plan, packed);
-    if ((rc = hipchk(hipMemcpyAsync(b->d_head, packed.data(), packed.size(), hipMemcpyHostToDevice, s), "upload plan")))
+    const std::unique_ptr<char[]> packed(new char[plan_bytes(plan)]);
+    pack_plan(plan, packed.get());
+    if ((rc = hipchk(hipMemcpyAsync(b->d_head, packed.get(), plan_bytes(plan), hipMemcpyHostToDevice, s), "upload plan")))
         return rc;
     if ((rc = hipchk(hipStreamSynchronize(s), "upload sync"))) return rc;
     b->opts = o;
