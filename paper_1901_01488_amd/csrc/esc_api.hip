@@ -14,6 +14,7 @@
 #include <utility>
 #include <vector>
 
+#include "esc_grid.h"
 #include "esc_host.h"
 #include "esc_kernels.h"
 #include "esc_runtime.h"
@@ -214,7 +215,10 @@ int esc_ctx_create(int device, esc_ctx **out)
     r = getenv("ESC_NONTEMPORAL");
     if (r) c->nt = atoi(r) != 0;
     r = getenv("ESC_BLOCKS_PER_CU");
-    if (r) c->bpc = atoi(r);
+    if (r) {
+        c->bpc = atoi(r);
+        c->bpc_set = true;
+    }
     r = getenv("ESC_MAT_BLOCKS_PER_CU");
     if (r) c->mat_bpc = atoi(r);
     r = getenv("ESC_DENSE_SHIFT");
@@ -322,13 +326,10 @@ static int count_launch(esc_ctx *ctx, const esc_table *t, const esc_pred *p, voi
         const bool udf = (P.flags & P_HAS_UDF) != 0;
         CountFn fn = count_fn(P.nslots, rpt, udf, tiles);
         const int occ = occupancy((const void *)fn, kScanBlock, 0);
-        int64_t grid = (int64_t)ctx->num_cus *
-                       (ctx->bpc > 0 ? count_bpc(ctx->count_variant, P.nslots, ctx->bpc, tiles) : occ);
         const int64_t blocks_needed = (L.ntiles + kScanBlock / 64 - 1) / (kScanBlock / 64);
-        // long programs on tables of up to two blocks per CU run them all at
-        // once (2.2M rows of the Section 1 selection: 28.6 us in two rounds, 23.5)
-        if (!tiles && P.ninsn > P.nslots && blocks_needed <= 2 * (int64_t)ctx->num_cus) grid = blocks_needed;
-        if (grid > blocks_needed) grid = blocks_needed;
+        const int64_t grid = count_grid(ctx->num_cus,
+                                        ctx->bpc > 0 ? count_bpc(ctx->count_variant, P.nslots, ctx->bpc, tiles) : occ,
+                                        ctx->bpc_set, !tiles && P.ninsn > P.nslots, blocks_needed);
         // a blocking count whose blocks each take one round gets a word of
         // each; on longer ones the atomics of the blocks' ends spread out
         if (host_words && !tiles && grid == blocks_needed && grid <= kCountParts) {

@@ -13,6 +13,7 @@ struct esc_ctx {
     int count_variant = 4;                  // count kernel shape (see count_rpt / count_bpc)
     int nt = 1;                             // streaming loads in the scans
     int bpc = 1;                            // count-kernel blocks per CU (0: occupancy)
+    bool bpc_set = false;                   // by ESC_BLOCKS_PER_CU
     int mat_bpc = 0;                        // materialize blocks per CU (0: occupancy)
     int dense_shift = 7;                    // projections of a tile read whole when >= tile rows >> shift qualify
     int cold_compact = 0;                   // a materialization without a count first: single pass (1) or count, scan, write (0)

@@ -1,0 +1,35 @@
+// Checks the numbers of blocks that the scans launch: the rules on sizes, and
+// that a setting is followed wherever it is made.  Exit code 1 on a difference.
+#include <stdio.h>
+
+#include <algorithm>
+
+#include "esc_grid.h"
+
+using namespace esc;
+
+static int bad = 0;
+
+static void expect(const char *what, int64_t got, int64_t want)
+{
+    if (got != want) {
+        printf("%s: %lld, expected %lld\n", what, (long long)got, (long long)want);
+        bad = 1;
+    }
+}
+
+int main()
+{
+    const int cus = 256;
+    for (int64_t needed : {1, 255, 256, 257, 511, 512, 513, 5000})
+        for (int per_cu : {1, 2, 3, 8}) {
+            const int64_t plain = std::min<int64_t>(needed, (int64_t)cus * per_cu);
+            expect("short count", count_grid(cus, per_cu, false, false, needed), plain);
+            expect("long count", count_grid(cus, per_cu, false, true, needed), needed <= 512 ? needed : plain);
+            // ESC_BLOCKS_PER_CU
+            expect("set, short count", count_grid(cus, per_cu, true, false, needed), plain);
+            expect("set, long count", count_grid(cus, per_cu, true, true, needed), plain);
+        }
+    if (!bad) printf("ok\n");
+    return bad;
+}
