@@ -490,16 +490,16 @@ static int materialize_launch(esc_ctx *ctx, const esc_table *t, const esc_pred *
         if ((rc = count_launch(ctx, t, p, dev_ws, ws_bytes, s, &h->result, true, expect))) return rc;
         // pass 2: offsets in row order (total in h->result and dev_total), by
         // the write pass itself for few tiles
-        const bool own = capacity > 0 && L.ntiles <= kOwnPrefixTiles;
+        const bool own = capacity > 0 && own_offsets(L.ntiles, ctx->mat_bpc);
         unsigned long long *const total = dev_total != &h->result ? dev_total : nullptr;
         if (!own) launch_scan(tiles, L.ntiles, offsets, h, total, s);
         // pass 3: write
         if (capacity > 0) {
             // one unit a wave, in as many blocks as that takes
             WriteFn fn = write_fn(rpt, own);
-            int64_t grid = (L.ntiles * 64 * rpt / 1024 + kScanBlock / 64 - 1) / (kScanBlock / 64);
-            if (!own && ctx->mat_bpc > 0)
-                grid = std::min(grid, (int64_t)ctx->num_cus * std::min(ctx->mat_bpc, occupancy((const void *)fn, kScanBlock, 0)));
+            const int64_t blocks_needed = (L.ntiles * 64 * rpt / 1024 + kScanBlock / 64 - 1) / (kScanBlock / 64);
+            const int64_t grid =
+                write_grid(ctx->num_cus, ctx->mat_bpc, occupancy((const void *)fn, kScanBlock, 0), blocks_needed);
             hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(kScanBlock), 0, s, bits, tiles, offsets, L.ntiles, pa,
                                dev_rowids, (unsigned long long)capacity, h, total);
         }

@@ -16,4 +16,24 @@ inline int64_t count_grid(int cus, int per_cu, bool set, bool long_plain, int64_
     return grid < needed ? grid : needed;
 }
 
+// Tiles up to which every block of the write pass finds its own offset (the
+// sum of the counts before it, read from the L2s) and no scan is launched.
+// The sums grow with tiles times blocks: counts and write passes of 0.05 % of
+// the rows, one column, with the scan and without, 6M rows 21 and 18 us, 12M
+// 28 and 26, 20M (9,766 tiles) 34 and 34, 28M 42 and 44, 40M 53 and 58.
+constexpr int64_t kOwnPrefixTiles = 12288;
+
+// Whether the blocks of the write pass find their own offsets: they then have to
+// be as many as its units fill, so not where ESC_MAT_BLOCKS_PER_CU (mat_bpc)
+// sets their number.
+inline bool own_offsets(int64_t ntiles, int mat_bpc) { return mat_bpc <= 0 && ntiles <= kOwnPrefixTiles; }
+
+// Blocks of the write pass for `needed` blocks' units, occ resident per CU.
+inline int64_t write_grid(int cus, int mat_bpc, int occ, int64_t needed)
+{
+    if (mat_bpc <= 0) return needed;
+    const int64_t grid = (int64_t)cus * (mat_bpc < occ ? mat_bpc : occ);
+    return grid < needed ? grid : needed;
+}
+
 }  // namespace esc

@@ -65,13 +65,6 @@ static_assert(sizeof(WsHeader) == 64, "workspace header is 64 bytes");
 typedef void (*CountFn)(const Program, const ColPtrs, int64_t, WsHeader *, unsigned long long *, const TileOut);
 typedef void (*WriteFn)(const uint32_t *, const uint32_t *, const uint32_t *, int64_t, const ProjArgs, int32_t *,
                         unsigned long long, WsHeader *, unsigned long long *);
-// Tiles up to which every block of the write pass finds its own offset (the
-// sum of the counts before it, read from the L2s) and no scan is launched.
-// The sums grow with tiles times blocks: counts and write passes of 0.05 % of
-// the rows, one column, with the scan and without, 6M rows 21 and 18 us, 12M
-// 28 and 26, 20M (9,766 tiles) 34 and 34, 28M 42 and 44, 40M 53 and 58.
-constexpr int64_t kOwnPrefixTiles = 12288;
-
 CountFn count_fn(int nslots, int rpt, bool udf, bool tiles);
 // a plain count whose out holds one host word per block
 CountFn count_parts_fn(int nslots, int rpt, bool udf);

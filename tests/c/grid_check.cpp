@@ -30,6 +30,15 @@ int main()
             expect("set, short count", count_grid(cus, per_cu, true, false, needed), plain);
             expect("set, long count", count_grid(cus, per_cu, true, true, needed), plain);
         }
+    for (int64_t tiles : {(int64_t)1, kOwnPrefixTiles - 1, kOwnPrefixTiles, kOwnPrefixTiles + 1, (int64_t)1000000}) {
+        expect("own offsets", own_offsets(tiles, 0), tiles <= kOwnPrefixTiles);
+        // ESC_MAT_BLOCKS_PER_CU: the scan's offsets, and its number of blocks
+        for (int set : {1, 2, 5}) expect("set, own offsets", own_offsets(tiles, set), 0);
+    }
+    for (int64_t needed : {1, 255, 1024, 6144, 100000}) {
+        expect("write pass", write_grid(cus, 0, 6, needed), needed);
+        for (int set : {1, 2, 5, 9}) expect("set, write pass", write_grid(cus, set, 6, needed), std::min<int64_t>(needed, 256 * std::min(set, 6)));
+    }
     if (!bad) printf("ok\n");
     return bad;
 }
