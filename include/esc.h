@@ -133,11 +133,15 @@ int esc_abi_version(void);
  * context (all optional; the defaults are the measured best on MI355X):
  *   ESC_COUNT_VARIANT 0..4   count kernel rows per lane and blocks per CU
  *                            (4: by column count, program length and use);
- *   ESC_BLOCKS_PER_CU n      count grid = n blocks per CU (default: occupancy);
- *   ESC_MAT_BLOCKS_PER_CU n  same for the materialization's write pass;
+ *   ESC_BLOCKS_PER_CU n      count grid = n blocks per CU (default: 1, and all at
+ *                            once for long programs on small tables; 0: occupancy);
+ *   ESC_MAT_BLOCKS_PER_CU n  write-pass grid = n blocks per CU, at most what fits
+ *                            (default: one wave per 1,024 rows);
  *   ESC_NONTEMPORAL 0|1      non-temporal column loads;
- *   ESC_DENSE_SHIFT 0..12    density 2^-shift (default 7) from which the policy's
- *                            cost model prices projected columns as read whole.
+ *   ESC_DENSE_SHIFT 0..12    density 2^-shift from which the write pass reads
+ *                            projected columns whole (default: an eighth of
+ *                            1,024 rows) and the policy's cost model prices
+ *                            them so (default 7, see esc_ctx_dense_fraction).
  * Outside the context: ESC_IN_HASH_MIN (compiler: smallest IN-list given a
  * slot table or bitmap, default 3, 0 = never) and ESC_AUTOTUNE_CACHE (a file
  * that keeps batched autotuning results between processes). */
@@ -145,10 +149,11 @@ int esc_ctx_create(int device, esc_ctx **out);
 int esc_ctx_destroy(esc_ctx *ctx);
 /* Number of compute units of the context's device. */
 int esc_ctx_num_cus(const esc_ctx *ctx, int *out);
-/* Fraction of a wave tile's rows from which the cost model prices a
- * materialization's projected columns as read whole rather than gathered (1/128
- * unless ESC_DENSE_SHIFT sets another power of two; the write pass itself
- * reads whole columns from an eighth of 1,024 rows on, whatever this is). */
+/* Fraction of a table's rows from which the policy's cost model prices a
+ * materialization's projected columns as read whole rather than gathered: 1/128
+ * unless ESC_DENSE_SHIFT sets another power of two.  The write pass itself
+ * gathers up to an eighth of 1,024 rows; between the two the calibrated line of
+ * the model's dense regime prices the gathers. */
 int esc_ctx_dense_fraction(const esc_ctx *ctx, double *out);
 
 /* ------------------------------------------------------------------ tables

@@ -222,7 +222,10 @@ int esc_ctx_create(int device, esc_ctx **out)
     r = getenv("ESC_MAT_BLOCKS_PER_CU");
     if (r) c->mat_bpc = atoi(r);
     r = getenv("ESC_DENSE_SHIFT");
-    if (r && atoi(r) >= 0 && atoi(r) <= 12) c->dense_shift = atoi(r);
+    if (r && atoi(r) >= 0 && atoi(r) <= 12) {
+        c->dense_shift = atoi(r);
+        c->dense_set = true;
+    }
     r = getenv("ESC_COLD_COMPACT");
     if (r) c->cold_compact = atoi(r) != 0;
     if (int rc = scratch_address(device, &c->scratch)) {
@@ -499,9 +502,11 @@ static int materialize_launch(esc_ctx *ctx, const esc_table *t, const esc_pred *
             WriteFn fn = write_fn(rpt, own);
             const int64_t blocks_needed = (L.ntiles * 64 * rpt / 1024 + kScanBlock / 64 - 1) / (kScanBlock / 64);
             const int64_t grid =
-                write_grid(ctx->num_cus, ctx->mat_bpc, occupancy((const void *)fn, kScanBlock, 0), blocks_needed);
+                write_grid(ctx->num_cus, ctx->mat_bpc,
+                           ctx->mat_bpc > 0 ? occupancy((const void *)fn, kScanBlock, 0) : 0, blocks_needed);
             hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(kScanBlock), 0, s, bits, tiles, offsets, L.ntiles, pa,
-                               dev_rowids, (unsigned long long)capacity, h, total);
+                               dev_rowids, (unsigned long long)capacity, dense_rows(ctx->dense_set, ctx->dense_shift), h,
+                               total);
         }
     }
     hipError_t e = hipGetLastError();

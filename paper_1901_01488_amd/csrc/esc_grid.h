@@ -36,4 +36,16 @@ inline int64_t write_grid(int cus, int mat_bpc, int occ, int64_t needed)
     return grid < needed ? grid : needed;
 }
 
+// Qualifying rows from which the write pass takes a unit's columns whole:
+// an eighth of its 1,024 rows (measured beside write_unit), or the fraction
+// 2^-shift that ESC_DENSE_SHIFT sets.
+constexpr int kUnitRows = 1024;
+
+inline uint32_t dense_rows(bool set, int shift)
+{
+    if (!set) return kUnitRows / 8;
+    const uint32_t rows = (uint32_t)kUnitRows >> shift;
+    return rows ? rows : 1u;
+}
+
 }  // namespace esc

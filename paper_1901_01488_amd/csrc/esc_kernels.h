@@ -64,7 +64,7 @@ static_assert(sizeof(WsHeader) == 64, "workspace header is 64 bytes");
 
 typedef void (*CountFn)(const Program, const ColPtrs, int64_t, WsHeader *, unsigned long long *, const TileOut);
 typedef void (*WriteFn)(const uint32_t *, const uint32_t *, const uint32_t *, int64_t, const ProjArgs, int32_t *,
-                        unsigned long long, WsHeader *, unsigned long long *);
+                        unsigned long long, uint32_t, WsHeader *, unsigned long long *);
 CountFn count_fn(int nslots, int rpt, bool udf, bool tiles);
 // a plain count whose out holds one host word per block
 CountFn count_parts_fn(int nslots, int rpt, bool udf);

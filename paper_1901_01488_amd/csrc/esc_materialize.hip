@@ -20,6 +20,7 @@
 #include <utility>
 
 #include "esc_device.h"
+#include "esc_grid.h"
 #include "esc_host.h"
 #include "esc_kernels.h"
 
@@ -180,7 +181,7 @@ __device__ __forceinline__ void wave_lds_fence()
 //
 // Where many rows of a unit qualify, reading and writing a row a lane is the
 // bound: four times the instructions of whole 16-byte groups, each touching
-// lines that the next one shares.  A unit of kDenseRows and more reads each
+// lines that the next one shares.  A unit of dense_rows() and more reads each
 // column's groups, places the values in LDS by rank and writes aligned
 // 16-byte groups (the last tile's units, whose rows may end inside a group,
 // excepted).  Two materializations on 40M rows, one, three and four columns,
@@ -189,12 +190,10 @@ __device__ __forceinline__ void wave_lds_fence()
 // 198, 353, 393.  The line at a quarter of the rows instead of an eighth cost
 // 18 to 22 % of them 3 to 10 % (200, 347, 402 against 195, 340, 366, with runs
 // of units a wave); below it both ways meet.
-constexpr int kUnitRows = 1024;
-constexpr uint32_t kDenseRows = kUnitRows / 8;
-
 template <int RPT>
 __device__ __forceinline__ void write_unit(uint32_t bits, int64_t base, unsigned long long p, const ProjArgs &pa,
-                                           int32_t *rowids, unsigned long long cap, bool whole, uint32_t *buf)
+                                           int32_t *rowids, unsigned long long cap, bool whole, uint32_t dense,
+                                           uint32_t *buf)
 {
     constexpr int NJ = kUnitRows / (4 * kWave);   // chunks of 256 rows
     const int lane = lane_id();
@@ -216,7 +215,7 @@ __device__ __forceinline__ void write_unit(uint32_t bits, int64_t base, unsigned
         first[j] = k;
     }
     const uint32_t avail = (uint32_t)(p + n <= cap ? n : cap - p);
-    if (whole && n >= kDenseRows) {
+    if (whole && n >= dense) {
         // one column at a time: its values (or the row ids) to their ranks in
         // LDS, then out in 16-byte groups; a run begins at word `head` of one
         auto column = [&](const uint32_t *src, uint32_t *dst, bool ids) {
@@ -334,7 +333,7 @@ __global__ __launch_bounds__(kScanBlock) void write_kernel(const uint32_t *__res
                                                            const uint32_t *__restrict__ counts,
                                                            const uint32_t *__restrict__ offsets, int64_t ntiles,
                                                            const ProjArgs pa, int32_t *rowids, unsigned long long cap,
-                                                           WsHeader *ws, unsigned long long *total)
+                                                           uint32_t dense, WsHeader *ws, unsigned long long *total)
 {
     constexpr int TILE = kWave * RPT;
     constexpr int NW = kScanBlock / kWave;
@@ -356,7 +355,7 @@ __global__ __launch_bounds__(kScanBlock) void write_kernel(const uint32_t *__res
             bits &= 0xffffu;
         }
         if (!__any(bits != 0u) || o0 >= cap) return;   // wave-uniform
-        write_unit<RPT>(bits, base, o0, pa, rowids, cap, t + 1 < ntiles, s_buf[wave]);
+        write_unit<RPT>(bits, base, o0, pa, rowids, cap, t + 1 < ntiles, dense, s_buf[wave]);
     };
     if constexpr (OWN) {
         constexpr int TPB = NW / UPT;   // tiles of a block

@@ -15,7 +15,8 @@ struct esc_ctx {
     int bpc = 1;                            // count-kernel blocks per CU (0: occupancy)
     bool bpc_set = false;                   // by ESC_BLOCKS_PER_CU
     int mat_bpc = 0;                        // materialize blocks per CU (0: occupancy)
-    int dense_shift = 7;                    // projections of a tile read whole when >= tile rows >> shift qualify
+    int dense_shift = 7;                    // the cost model's dense fraction is 2^-dense_shift (also the single pass's line)
+    bool dense_set = false;                 // by ESC_DENSE_SHIFT: the write pass's line too (dense_rows)
     int cold_compact = 0;                   // a materialization without a count first: single pass (1) or count, scan, write (0)
     void *scratch = nullptr;                // this device's static scratch (esc_materialize_noalloc)
     hipEvent_t slot_event[ESC_COUNT_SLOTS] = {};   // esc_count_begin / esc_count_end

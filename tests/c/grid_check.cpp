@@ -39,6 +39,9 @@ int main()
         expect("write pass", write_grid(cus, 0, 6, needed), needed);
         for (int set : {1, 2, 5, 9}) expect("set, write pass", write_grid(cus, set, 6, needed), std::min<int64_t>(needed, 256 * std::min(set, 6)));
     }
+    expect("dense rows", dense_rows(false, 7), 128);
+    // ESC_DENSE_SHIFT
+    for (int shift = 0; shift <= 12; shift++) expect("set, dense rows", dense_rows(true, shift), std::max(1, 1024 >> shift));
     if (!bad) printf("ok\n");
     return bad;
 }

@@ -1,5 +1,6 @@
 """The write pass under its settings (ESC_MAT_BLOCKS_PER_CU: fewer blocks, which
-go on to further units), sparse, dense and mixed units; row ids and values bit
+go on to further units; ESC_DENSE_SHIFT: another line between the two ways of
+writing a unit), sparse, dense and mixed units; row ids and values bit
 for bit against torch's own selection."""
 import pytest
 
@@ -8,7 +9,8 @@ from paper_1901_01488_amd import esc
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("name,value", [("ESC_MAT_BLOCKS_PER_CU", "1"), ("ESC_MAT_BLOCKS_PER_CU", "3")])
+@pytest.mark.parametrize("name,value", [("ESC_MAT_BLOCKS_PER_CU", "1"), ("ESC_MAT_BLOCKS_PER_CU", "3"), ("ESC_DENSE_SHIFT", "0"),
+                                        ("ESC_DENSE_SHIFT", "7"), ("ESC_DENSE_SHIFT", "12")])
 @pytest.mark.parametrize("rows", [1, 2049, 70_001, 3_000_007])
 def test_settings(monkeypatch, rows, name, value):
     import torch
