@@ -503,7 +503,8 @@ static int materialize_launch(esc_ctx *ctx, const esc_table *t, const esc_pred *
             const int64_t blocks_needed = (L.ntiles * 64 * rpt / 1024 + kScanBlock / 64 - 1) / (kScanBlock / 64);
             const int64_t grid =
                 write_grid(ctx->num_cus, ctx->mat_bpc,
-                           ctx->mat_bpc > 0 ? occupancy((const void *)fn, kScanBlock, 0) : 0, blocks_needed);
+                           ctx->mat_bpc > 0 ? occupancy((const void *)fn, kScanBlock, 0) : 0,
+                           !own && few_written(capacity, t->nrows), blocks_needed);
             hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(kScanBlock), 0, s, bits, tiles, offsets, L.ntiles, pa,
                                dev_rowids, (unsigned long long)capacity, dense_rows(ctx->dense_set, ctx->dense_shift), h,
                                total);

@@ -29,12 +29,20 @@ constexpr int64_t kOwnPrefixTiles = 12288;
 inline bool own_offsets(int64_t ntiles, int mat_bpc) { return mat_bpc <= 0 && ntiles <= kOwnPrefixTiles; }
 
 // Blocks of the write pass for `needed` blocks' units, occ resident per CU.
-inline int64_t write_grid(int cus, int mat_bpc, int occ, int64_t needed)
+// sparse: few_written().
+inline int64_t write_grid(int cus, int mat_bpc, int occ, bool sparse, int64_t needed)
 {
-    if (mat_bpc <= 0) return needed;
-    const int64_t grid = (int64_t)cus * (mat_bpc < occ ? mat_bpc : occ);
+    int64_t grid = needed;
+    if (mat_bpc > 0) grid = (int64_t)cus * (mat_bpc < occ ? mat_bpc : occ);
+    else if (sparse) grid = 16 * (int64_t)cus;
     return grid < needed ? grid : needed;
 }
+
+// Whether the outputs have room for so few of the rows that most units hold
+// little: then waves that go on to further units, their masks read ahead, cost
+// less than a launch for each (with its count, 0.001 % of the rows, one column,
+// 100M rows 96 us, 100 with a wave for each unit; 200M 188 and 197).
+inline bool few_written(uint64_t capacity, int64_t nrows) { return capacity < (uint64_t)nrows / 64; }
 
 // Qualifying rows from which the write pass takes a unit's columns whole:
 // an eighth of its 1,024 rows (measured beside write_unit), or the fraction

@@ -35,10 +35,16 @@ int main()
         // ESC_MAT_BLOCKS_PER_CU: the scan's offsets, and its number of blocks
         for (int set : {1, 2, 5}) expect("set, own offsets", own_offsets(tiles, set), 0);
     }
-    for (int64_t needed : {1, 255, 1024, 6144, 100000}) {
-        expect("write pass", write_grid(cus, 0, 6, needed), needed);
-        for (int set : {1, 2, 5, 9}) expect("set, write pass", write_grid(cus, set, 6, needed), std::min<int64_t>(needed, 256 * std::min(set, 6)));
-    }
+    for (int64_t needed : {1, 255, 1024, 6144, 100000})
+        for (bool sparse : {false, true}) {
+            expect("write pass", write_grid(cus, 0, 6, sparse, needed), sparse ? std::min<int64_t>(needed, 4096) : needed);
+            for (int set : {1, 2, 5, 9})
+                expect("set, write pass", write_grid(cus, set, 6, sparse, needed), std::min<int64_t>(needed, 256 * std::min(set, 6)));
+        }
+    expect("few written", few_written(0, 64), 1);
+    expect("few written", few_written(1, 64), 0);
+    expect("few written", few_written(1562499, 100000000), 1);
+    expect("few written", few_written(1562500, 100000000), 0);
     expect("dense rows", dense_rows(false, 7), 128);
     // ESC_DENSE_SHIFT
     for (int shift = 0; shift <= 12; shift++) expect("set, dense rows", dense_rows(true, shift), std::max(1, 1024 >> shift));
