@@ -149,11 +149,10 @@ int esc_ctx_create(int device, esc_ctx **out);
 int esc_ctx_destroy(esc_ctx *ctx);
 /* Number of compute units of the context's device. */
 int esc_ctx_num_cus(const esc_ctx *ctx, int *out);
-/* Fraction of a table's rows from which the policy's cost model prices a
- * materialization's projected columns as read whole rather than gathered: 1/128
- * unless ESC_DENSE_SHIFT sets another power of two.  The write pass itself
- * gathers up to an eighth of 1,024 rows; between the two the calibrated line of
- * the model's dense regime prices the gathers. */
+/* Selectivity at which the policy's cost model changes from its sparse to its
+ * dense line: 1/128 unless ESC_DENSE_SHIFT sets another power of two.  (The
+ * write pass gathers up to an eighth of 1,024 rows; the dense line is fitted
+ * over both of its ways.) */
 int esc_ctx_dense_fraction(const esc_ctx *ctx, double *out);
 
 /* ------------------------------------------------------------------ tables
@@ -613,8 +612,8 @@ int esc_join_count(esc_ctx *ctx, const esc_table *probe, const int32_t *key_cols
  * read by a re-read of the table and r later uses:
  *   without the temporary table, every use re-reads the table:
  *     T_scan = r * nrows * 4k / scan_bytes_per_s
- *   with it (the materialization gathers projected values while
- *   s < dense_fraction and reads the projected columns whole above):
+ *   with it (a line in the rows written while s < dense_fraction; above it
+ *   rows share what is read, priced as the projected columns and a line):
  *     T_mat  = fixed_s + count * sparse_row_s          (count = 0 or s < dense_fraction)
  *            = fixed_s + nrows * 4p / dense_bytes_per_s + count * dense_row_s   (otherwise)
  *            + r * count * 4 (1 + p) / tmp_bytes_per_s     (reading row ids and values)
@@ -624,7 +623,7 @@ typedef struct {
     double scan_bytes_per_s;   /* streaming read rate of a selection scan */
     double fixed_s;            /* materialization cost per call (launches, offsets) */
     double sparse_row_s;       /* per qualifying row while projected values are gathered */
-    double dense_fraction;     /* selectivity from which projected columns are read whole */
+    double dense_fraction;     /* selectivity from which the dense line holds */
     double dense_bytes_per_s;  /* read rate of whole projected columns */
     double dense_row_s;        /* per qualifying row when columns are read whole */
     double tmp_bytes_per_s;    /* read rate of a temporary table */

@@ -98,67 +98,6 @@ __global__ __launch_bounds__(1024) void scan_kernel(const uint32_t *counts, int6
 
 // ------------------------------------------------------------------ write
 
-// Stages up to 256 values of the current chunk in the wave's LDS buffer at
-// their compacted slots, then writes the first `avail` of them to dst with
-// consecutive lanes on consecutive words (coalesced).
-template <typename V>
-__device__ __forceinline__ void stage_and_flush(uint32_t *buf, uint32_t nib, const uint32_t (&slot)[4], V &&val,
-                                                uint32_t *dst, uint32_t avail)
-{
-#pragma unroll
-    for (int e = 0; e < 4; e++)
-        if ((nib >> e) & 1u) buf[slot[e]] = val(e);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    for (uint32_t i = lane_id(); i < avail; i += kWave) dst[i] = buf[i];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Writes the qualifying rows of one wave tile (lane masks `bits`, rows from
-// `base`) at output positions p onwards, in row order, at most up to `cap`.
-// Chunk j of the tile (256 rows) is compacted in LDS (rank of a row = lanes
-// below, from ballot masks, then e) and each output column is written as one
-// contiguous run.  proj(q, j, e, r0) gives projected column q's value at row
-// r0 + e of chunk j.
-template <int RPT, typename Proj>
-__device__ __forceinline__ void write_tile(uint32_t bits, int64_t base, unsigned long long p, const ProjArgs &pa,
-                                           int32_t *rowids, unsigned long long cap, uint32_t *buf, Proj &&proj)
-{
-    constexpr int NJ = RPT / 4;
-    const int lane = lane_id();
-#pragma unroll
-    for (int j = 0; j < NJ; j++) {
-        const uint32_t nib = (bits >> (4 * j)) & 0xfu;
-        uint32_t pre = 0, tot = 0;
-#pragma unroll
-        for (int e = 0; e < 4; e++) {
-            // set bits of the ballot in the lanes below this one (mbcnt: no
-            // 64-bit shift by a per-lane amount)
-            const uint64_t b = __ballot((nib >> e) & 1u);
-            pre = __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, pre));
-            tot += (uint32_t)__popcll(b);
-        }
-        if (tot == 0) continue;
-        if (p >= cap) break;
-        const uint32_t avail = (uint32_t)(p + tot <= cap ? tot : cap - p);
-        uint32_t slot[4];
-        uint32_t k = pre;
-#pragma unroll
-        for (int e = 0; e < 4; e++) {
-            slot[e] = k;
-            k += (nib >> e) & 1u;
-        }
-        const int64_t r0 = base + (int64_t)j * (4 * kWave) + lane * 4;   // row of e = 0
-        if (rowids)
-            stage_and_flush(buf, nib, slot, [&](int e) { return (uint32_t)(r0 + e); }, (uint32_t *)rowids + p, avail);
-        for (int q = 0; q < pa.nproj; q++) proj(q, j, r0, nib, slot, pa.dst[q] + p, avail);
-        p += tot;
-    }
-}
-
 // Orders a wave's LDS accesses before and after it.
 __device__ __forceinline__ void wave_lds_fence()
 {
@@ -418,6 +357,67 @@ __global__ __launch_bounds__(kScanBlock) void write_kernel(const uint32_t *__res
 
 // ------------------------------------------------------------------ single-pass compaction
 
+// Stages up to 256 values of the current chunk in the wave's LDS buffer at
+// their compacted slots, then writes the first `avail` of them to dst with
+// consecutive lanes on consecutive words (coalesced).
+template <typename V>
+__device__ __forceinline__ void stage_and_flush(uint32_t *buf, uint32_t nib, const uint32_t (&slot)[4], V &&val,
+                                                uint32_t *dst, uint32_t avail)
+{
+#pragma unroll
+    for (int e = 0; e < 4; e++)
+        if ((nib >> e) & 1u) buf[slot[e]] = val(e);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (uint32_t i = lane_id(); i < avail; i += kWave) dst[i] = buf[i];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Writes the qualifying rows of one wave tile (lane masks `bits`, rows from
+// `base`) at output positions p onwards, in row order, at most up to `cap`.
+// Chunk j of the tile (256 rows) is compacted in LDS (rank of a row = lanes
+// below, from ballot masks, then e) and each output column is written as one
+// contiguous run.  proj(q, j, e, r0) gives projected column q's value at row
+// r0 + e of chunk j.
+template <int RPT, typename Proj>
+__device__ __forceinline__ void write_tile(uint32_t bits, int64_t base, unsigned long long p, const ProjArgs &pa,
+                                           int32_t *rowids, unsigned long long cap, uint32_t *buf, Proj &&proj)
+{
+    constexpr int NJ = RPT / 4;
+    const int lane = lane_id();
+#pragma unroll
+    for (int j = 0; j < NJ; j++) {
+        const uint32_t nib = (bits >> (4 * j)) & 0xfu;
+        uint32_t pre = 0, tot = 0;
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            // set bits of the ballot in the lanes below this one (mbcnt: no
+            // 64-bit shift by a per-lane amount)
+            const uint64_t b = __ballot((nib >> e) & 1u);
+            pre = __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, pre));
+            tot += (uint32_t)__popcll(b);
+        }
+        if (tot == 0) continue;
+        if (p >= cap) break;
+        const uint32_t avail = (uint32_t)(p + tot <= cap ? tot : cap - p);
+        uint32_t slot[4];
+        uint32_t k = pre;
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            slot[e] = k;
+            k += (nib >> e) & 1u;
+        }
+        const int64_t r0 = base + (int64_t)j * (4 * kWave) + lane * 4;   // row of e = 0
+        if (rowids)
+            stage_and_flush(buf, nib, slot, [&](int e) { return (uint32_t)(r0 + e); }, (uint32_t *)rowids + p, avail);
+        for (int q = 0; q < pa.nproj; q++) proj(q, j, r0, nib, slot, pa.dst[q] + p, avail);
+        p += tot;
+    }
+}
+
 // Status word of a wave tile in the single-pass compaction: flag in the top
 // two bits (0 not yet published, 1 the tile's own count, 2 the inclusive
 // prefix of all tiles up to it), the value in the low 62 bits.
@@ -431,8 +431,8 @@ constexpr unsigned long long kStValue = (1ull << 62) - 1ull;
 // predecessor that has published its inclusive prefix ends the walk; one
 // that has published only its count adds it and the walk continues).  Every
 // predecessor was taken by a running wave before this tile, so every wait
-// ends.  The qualifying rows are then written at that offset exactly as the
-// write pass does, taking the projected values of predicate columns from
+// ends.  The qualifying rows are then written at that offset, 256 rows staged
+// at a time, taking the projected values of predicate columns from
 // registers.  status (ntiles words) and ctr must be zero at launch.
 template <int K, int RPT, bool UDF>
 __global__ __launch_bounds__(kScanBlock) void compact_kernel(const Program P, const ColPtrs cp, int64_t n,

@@ -359,7 +359,7 @@ class Context:
         return out.value
 
     def dense_fraction(self):
-        """Tile density from which the materialization reads projected columns whole."""
+        """Selectivity at which the policy's cost model changes from its sparse to its dense line."""
         v = ctypes.c_double()
         check(lib().esc_ctx_dense_fraction(self.h, ctypes.byref(v)))
         return v.value

@@ -11,10 +11,12 @@ device with the library's own kernels:
                     already done, so only the offsets and the write pass run);
   sparse_row_s      a least-squares line through the materialization times
                     of `lt k` selections on the permutation key below the
-                    dense fraction (projected values gathered);
+                    dense fraction (a sector of 64 bytes for every value);
   dense_bytes_per_s, dense_row_s
-                    a line through those above it (projected columns read
-                    whole: the intercept is the column read);
+                    a line through those above it, where rows share sectors
+                    and, from an eighth of the rows on, the write pass reads
+                    the projected columns whole (the intercept stands for
+                    the columns' read);
   tmp_bytes_per_s   counts over the temporary table of the largest of them
                     (row ids and projected columns).
 Every count and materialization runs inside libesc; this module only
@@ -55,10 +57,8 @@ def calibrate(ctx, table: esc.Table, key_col, proj, scan_cols,
     """Cost model for materializing `proj` (projected column indices) of
     selections on `table`, whose column key_col holds a permutation of
     0..nrows-1 and whose first scan_cols columns are non-negative ints.
-    `lt k` selections on the key spread their rows evenly, so a selectivity
-    below the dense fraction gathers projected values row by row and one
-    above it reads the projected columns whole.  Returns (esc.CostModel,
-    details)."""
+    `lt k` selections on the key spread their rows evenly.  Returns
+    (esc.CostModel, details)."""
     import torch
     dev = table.cols[0].device
     n = table.nrows
