@@ -116,7 +116,7 @@ __device__ __forceinline__ void wave_lds_fence()
 // ranks, one read per column): values need no staging, so a wave keeps 12
 // reads per lane in flight in few registers.  Staging each 256-row chunk of
 // a tile column by column took 131 us for the temporary tables of the star
-// selections (60M rows, 0.9-8 % of them, three columns), against 81 us now.
+// selections (60M rows, 0.9-8 % of them, three columns), against 82 us now.
 //
 // Where many rows of a unit qualify, reading and writing a row a lane is the
 // bound: four times the instructions of whole 16-byte groups, each touching
